@@ -131,8 +131,12 @@ typedef struct {
                            residual exceeds the segment's final recurrence
                            residual by more than 2x (drift), when the next
                            segment restarts; 0                              */
-  int32_t check_every;  /* iterations per captured chunk (one HIP graph of
-                           check_every iterations of every kernel); 32      */
+  int32_t check_every;  /* iterations per chunk: one launch of the persistent
+                           chunk kernel where it applies (rows_per_thread,
+                           w_mode, op_fused, op_rows, op_group and update_ws
+                           all 0 and a batch whose blocks are all resident at
+                           once), else one HIP graph of check_every iterations
+                           of every kernel; 32                              */
   int32_t rows_per_thread; /* rows per thread of the per-instance iteration
                            kernels (tile height 256 or 512 rows): 1 or 2, or
                            0 = tuned on the first solve of each

@@ -3,7 +3,8 @@
 The library is split into translation units that compile in parallel: the
 host runtime with the setup kernels (adef2.hip), the per-instance iteration
 kernels once per vector type / panel type / tile height (iter_inst.hip with
--D defines) and the tile-major iteration kernels (iter_bt.hip).  Objects go
+-D defines), the persistent chunk kernel likewise (iter_persist.hip) and the
+tile-major iteration kernels (iter_bt.hip).  Objects go
 to _build/ next to this file; the shared library is linked in place.
 """
 import os
@@ -29,6 +30,10 @@ for v, m, tag in (("double", "double", "dd"), ("double", "float", "df"), ("float
     for rpt in (1, 2):
         UNITS.append((f"iter_{tag}_r{rpt}", "iter_inst.hip",
                       [f"-DITER_V={v}", f"-DITER_M={m}", f"-DITER_RPT={rpt}"]))
+for v, m, tag in (("double", "double", "dd"), ("double", "float", "df"), ("float", "float", "ff")):
+    for r in (256, 512, 1024):
+        UNITS.append((f"iter_persist_{tag}_{r}", "iter_persist.hip",
+                      [f"-DITER_V={v}", f"-DITER_M={m}", f"-DITER_R={r}"]))
 UNITS.append(("iter_bt", "iter_bt.hip", []))
 
 

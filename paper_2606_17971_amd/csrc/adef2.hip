@@ -12,6 +12,7 @@
 
 #include "../../include/adef2.h"
 #include "dev_learned.h"
+#include "dev_persist.h"
 #include "iter_tab.h"
 
 using namespace adef2;
@@ -60,12 +61,12 @@ constexpr double FP32_COND = 1e-3 / 5.96e-8;   // learned cond(E) bound with FP3
 
 enum KernelId { KI_INIT = 0, KI_INIT2, KI_PUPDATE, KI_SPMV, KI_UPDATE, KI_RESID, KI_ACCUM,
                 KI_GRAM, KI_COARSE, KI_COMPACT, KI_UPDATE_NW, KI_ZPROJ, KI_PUPDATE_BT, KI_ZPROJ_BT,
-                KI_PUPDATE_TM, KI_UPDATE_TM, KI_FINISH_TM, KI_STENCIL, KI_OPFUSED, KI_COUNT };
+                KI_PUPDATE_TM, KI_UPDATE_TM, KI_FINISH_TM, KI_STENCIL, KI_OPFUSED, KI_CHUNK, KI_COUNT };
 static_assert(KI_COUNT <= ADEF2_STATS_KERNELS, "adef2_stats holds ADEF2_STATS_KERNELS entries");
 const char* kKernelNames[KI_COUNT] = {"init", "init2", "pupdate", "spmv", "update", "resid64",
                                       "accumulate", "spmm_gram", "coarse", "compact", "update_nw",
                                       "zproj", "pupdate_bt", "zproj_bt", "pupdate_tm", "update_tm",
-                                      "finish_tm", "stencil1", "opfused"};
+                                      "finish_tm", "stencil1", "opfused", "chunk"};
 
 }  // namespace
 
@@ -217,6 +218,15 @@ struct adef2_ctx {
   struct Tuned { int B, prec, KP, fact, tm; int64_t N; int rpt, wfree; float ms[10]; int opo, opf, opg; float ms_op[7];
                  int uwo, uws; float ms_uw[2]; int fro, fwo; };
   std::vector<Tuned> tuned;      // autotuned variants per configuration
+  // persistent chunk kernel (k_persist): rows per block, 0 = one kernel per
+  // step; its exchange buffers, launches so far and arrivals they add up to
+  int ps_rows = 0;
+  int n_cu = 0;
+  unsigned* ps_flags = nullptr;
+  double *ps_pw = nullptr, *ps_dots = nullptr;
+  unsigned* ps_shake = nullptr;
+  size_t ps_tiles = 0, ps_vals = 0;   // tiles, and tiles times values, allocated
+  unsigned ps_seq = 0, ps_base = 0;
   RedGeom g_iter{};
   int gram_blocks = 0;
   RedGeom g_gram{};
@@ -321,6 +331,7 @@ void free_all(adef2_ctx* c) {
   F(c->W64); F(c->W32); F(c->dinv64); F(c->dinv32); F(c->x64); F(c->r64); F(c->x0pad);
   F(c->t64); F(c->t32); F(c->Tm); F(c->dia1_64); F(c->dia1_32);
   F(c->part); F(c->ctr);
+  F(c->ps_flags); F(c->ps_pw); F(c->ps_dots); F(c->ps_shake);
   F(c->Phi); F(c->mlp); F(c->mlp_bf); F(c->mlp_g); F(c->mlp_m); F(c->mlp_v); F(c->theta_tr);
   F(c->Htr); F(c->Ntr); F(c->gtr); F(c->e0tr); F(c->bxtr); F(c->act); F(c->mout); F(c->dout); F(c->dA1);
   F(c->dA2); F(c->lossv); F(c->Zb64); F(c->Zb32); F(c->mu64); F(c->eigf); F(c->bnd); F(c->hb); F(c->zero64);
@@ -480,6 +491,7 @@ int opf_default_rows(const adef2_ctx* c) {
 // opf: rows of the fused operator pass's tiles (0 = two passes); opg: its
 // instances per block
 void set_variant(adef2_ctx* c, int rpt, int wfree, int opf = 0, int opg = 1, int uws = 0) {
+  c->ps_rows = 0;
   c->rpt = rpt;
   c->wfree = wfree;
   c->of_rows = opf;
@@ -942,6 +954,123 @@ int chunk_graph(adef2_ctx* c, const IterArgs<V, M>& a, int chunk, int variant, c
   return ADEF2_OK;
 }
 
+// ------------------------------------------------- persistent chunk kernel
+template <typename V, typename M>
+PersistFn<V, M> persist_fn(int KP, int rows, int form) {
+  switch (rows) {
+    case 256: return pick_persist<V, M, 256>(KP, form);
+    case 512: return pick_persist<V, M, 512>(KP, form);
+    default: return pick_persist<V, M, 1024>(KP, form);
+  }
+}
+
+// form of W^T z in the persistent chunk kernel
+int persist_form(const adef2_ctx* c) {
+  if (c->KP == 0) return PS_STORED;
+  if (c->ne > 0) return PS_SPEC;
+  if (!mat64(c->prec)) return PS_STORED;
+  // Z^T (S z) once the panels W and Z no longer come from the caches fast
+  // enough: one more exchange (3 us) against reading W.  Per iteration, stored
+  // against free: 11.2 / 13.1 us at 63^2, k = 16 (1 MB); 22.6 / 25.9 us at
+  // 255^2, k = 40 (42 MB); 36.9 / 33.1 us at 127^2 x 16, k = 40 (88 MB);
+  // 53.4 / 49.3 us at 100^2 x 30, k = 40 (99 MB)
+  const double panels = 8.0 * c->N * c->KP * (c->B + (c->zs ? c->B : 1));
+  return panels > 64e6 ? PS_FREE : PS_STORED;
+}
+
+int op_reach(const std::vector<int>& offs) {
+  int r = 0;
+  for (int o : offs) r = std::max(r, std::abs(o));
+  return r;
+}
+
+// the factored operator's inner product stays in LDS while its halo is no
+// longer than the tile
+bool persist_fused(const adef2_ctx* c, int rows) { return c->factored && 2 * op_reach(c->offs) <= 2 * rows; }
+
+size_t persist_lds(const adef2_ctx* c, int rows) {
+  return sizeof(double) * ((size_t)c->KP * c->KP + (persist_fused(c, rows) ? rows + 2 * op_reach(c->offs) : 0));
+}
+
+// rows per block of the persistent chunk kernel for the current restriction,
+// 0 when it does not apply (not every block would be resident at once).
+// Smaller tiles give each block less to do, but every block adds one partial
+// sum per tile and a compute unit with two blocks sets the pace of all: 256
+// rows up to 128 blocks (63^2: 11.2 us an iteration, 12.1 with 512; 255^2:
+// 26.6 us with 255 blocks, 22.6 with 512 rows), 512 rows up to one block per
+// compute unit, else 1024 (191^2 x 5: 24.2 us, 25.1 with 512).
+int persist_rows(adef2_ctx* c) {
+  const adef2_opts& o = c->o;
+  if (o.w_mode || o.rows_per_thread || o.op_fused || o.op_rows || o.op_group || o.update_ws) return 0;
+  // FP32 panels in the boundary form: every column has to be in it
+  if (c->ne > 0 && (c->zs != 0 || c->n_eig != c->k)) return 0;
+  if (!c->n_cu) {
+    hipDeviceProp_t prop;
+    if (hipGetDeviceProperties(&prop, c->dev) != hipSuccess) return 0;
+    c->n_cu = prop.multiProcessorCount;
+  }
+  for (int R : {256, 512, 1024}) {
+    const int64_t blocks = cdiv(c->N, (int64_t)R) * c->B;
+    if ((R == 256 && blocks > 128) || (R == 512 && blocks > c->n_cu)) continue;
+    const int form = persist_form(c);
+    const void* fn = mat64(c->prec)   ? (const void*)persist_fn<double, double>(c->KP, R, form)
+                     : vec64(c->prec) ? (const void*)persist_fn<double, float>(c->KP, R, form)
+                                      : (const void*)persist_fn<float, float>(c->KP, R, form);
+    const size_t lds = persist_lds(c, R);
+    int per = 0;
+    if (lds > 64 * 1024 ||
+        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, PS_TB, lds) != hipSuccess)
+      return 0;
+    if (blocks <= (int64_t)per * c->n_cu) return R;
+  }
+  return 0;
+}
+
+// exchange buffers for the current batch
+int persist_buffers(adef2_ctx* c) {
+  const size_t tiles = (size_t)cdiv(c->N, (int64_t)c->ps_rows) * c->B;
+  const size_t vals = tiles * (2 * c->KP + 2);
+  int rc;
+  if (!c->ps_shake) {
+    if ((rc = dalloc(c, &c->ps_shake, PS_WORDS))) return rc;
+    fill<unsigned>(c, c->ps_shake, PS_WORDS, 0u);
+    c->ps_seq = c->ps_base = 0;
+  }
+  if (tiles > c->ps_tiles) {
+    c->ps_tiles = 0;
+    if ((rc = dalloc(c, &c->ps_flags, tiles)) || (rc = dalloc(c, &c->ps_pw, 3 * tiles))) return rc;
+    c->ps_tiles = tiles;
+  }
+  if (vals > c->ps_vals) {
+    c->ps_vals = 0;
+    if ((rc = dalloc(c, &c->ps_dots, 3 * vals))) return rc;
+    c->ps_vals = vals;
+  }
+  return ADEF2_OK;
+}
+
+template <typename V, typename M>
+void launch_persist(adef2_ctx* c, const IterArgs<V, M>& a, int chunk, hipStream_t s) {
+  PersistArgs pa{};
+  pa.flags = c->ps_flags;
+  pa.pw = c->ps_pw;
+  pa.dots = c->ps_dots;
+  pa.shake = c->ps_shake;
+  pa.nt = (int)cdiv(c->N, (int64_t)c->ps_rows);
+  pa.nt_pad = (int)cdiv(pa.nt, 8) * 8;
+  pa.nblk = (unsigned)(pa.nt * c->B);
+  pa.seq = ++c->ps_seq;
+  pa.base = c->ps_base;
+  c->ps_base += pa.nblk;
+  pa.chunk = chunk;
+  pa.reach = op_reach(c->offs);
+  pa.reach1 = c->factored ? op_reach(c->offs1) : 0;
+  pa.fused = persist_fused(c, c->ps_rows);
+  hipLaunchKernelGGL((persist_fn<V, M>(c->KP, c->ps_rows, persist_form(c))), dim3((unsigned)(pa.nt_pad * c->B)),
+                     dim3(PS_TB), persist_lds(c, c->ps_rows), s, a, pa);
+}
+
 // max_chunks > 0 stops after that many chunks (tuning trials).
 template <typename V, typename M>
 // b_outer != null: refinement with sweep transitions inside the chunks (each
@@ -1014,8 +1143,16 @@ int run_sweep(adef2_ctx* c, const double* src, const double* x0pad, double thres
   const int chunk = std::max(1, c->o.check_every);
   // one chunk of iterations on stream s (kernel arguments are the same for
   // every iteration: all per-iteration state lives in device memory)
+  bool persist = c->ps_rows > 0;
+  if (persist) {
+    int rc = persist_buffers(c);
+    if (rc) return rc;
+  }
   auto launch_chunk = [&](hipStream_t s) {
-    for (int it = 0; it < chunk; ++it) {
+    if (persist)
+      timed(c, KI_CHUNK, chunk * (bm.pupdate + bm.stencil + bm.spmv + bm.update),
+            [&] { launch_persist<V, M>(c, a, chunk, s); });
+    for (int it = 0; it < (persist ? 0 : chunk); ++it) {
       if constexpr (sizeof(V) == 8) {
         if (tm)
           timed(c, KI_PUPDATE_TM, bm.pupdate,
@@ -1088,16 +1225,18 @@ int run_sweep(adef2_ctx* c, const double* src, const double* x0pad, double thres
     }
   };
   hipGraphExec_t gexec = nullptr;
-  if (c->o.graph && !c->o.profile) {
+  auto make_graph = [&]() -> int {
+    if (!c->o.graph || c->o.profile || persist) return ADEF2_OK;
     // the key names every choice that changes the launches: the W mode code
     // itself (w_mode 4 and 5 differ only in the stencil kernels), the
     // operator form and the boundary form
-    int rc = chunk_graph<V, M>(c, a, chunk,
+    return chunk_graph<V, M>(c, a, chunk,
                                (c->uws << 13) | ((b_outer ? 1 : 0) << 12) | (c->opg << 9) | ((int)c->opf << 8) | (c->wfree << 4) |
                                    ((int)tm << 3) | ((int)bt << 2) | ((int)wfree << 1) | (c->ne > 0 ? 1 : 0),
                                b_outer, launch_chunk, &gexec);
-    if (rc) return rc;
-  }
+  };
+  int grc = make_graph();
+  if (grc) return grc;
   // Convergence is decided on the device (finished instances' blocks exit at
   // once); the host only has to notice that every instance is done.  Between
   // polls it enqueues as many chunks as the slowest instance is estimated to
@@ -1112,6 +1251,17 @@ int run_sweep(adef2_ctx* c, const double* src, const double* x0pad, double thres
     bool ad = false;
     int rc = poll(c, b_outer != nullptr, &ad);
     if (rc) return rc;
+    if (persist) {
+      // a chunk that was called off (not every block got a compute unit in
+      // time) has changed nothing: go on with one kernel per step
+      int off = 0;
+      for (int m = 0; m < c->B; ++m) off = std::max(off, (int)c->inst_h[m].off);
+      if (off == 2) return fail(c, ADEF2_E_HIP, "persistent iteration kernel: a block did not answer");
+      if (off == 1) {
+        persist = false;
+        if ((grc = make_graph())) return grc;
+      }
+    }
     if (ad) break;
     // every instance stops at maxit on the device; this guards the host loop
     if (launched > (int64_t)c->o.maxit + (int64_t)(pmax + 2) * chunk)
@@ -1168,7 +1318,7 @@ int reset_solve_state(adef2_ctx* c) {
     Inst& s = c->inst_h[m];
     s.iters = 0; s.sweep_iters = 0; s.done = 0; s.outer_done = 0; s.status = 0; s.sweeps = 0;
     s.has_dir = 0; s.rho_end = 0.0; s.stall = 0; s.rr64_best = INFINITY; s.drift = 0;
-    s.capped = 0; s.trans = 0;
+    s.capped = 0; s.trans = 0; s.off = 0;
     s.rr = 0; s.rr64 = 0; s.bb64 = 0;
     const double t = m < (int)c->tol_h.size() ? c->tol_h[m] : 1e-8;
     s.tol2 = t * t;
@@ -1196,6 +1346,12 @@ int choose_variant(adef2_ctx* c, const double* b) {
                 "the tile-major boundary-form update needs FP32 panels with FP64 vectors (MIXED_REFINE), "
                 "reference modes shared by all instances that are eigenvectors of the reference operator, "
                 "and w_boundary enabled");
+  if (const int R = persist_rows(c)) {
+    // (the variant of the kernel-per-step form, in case a chunk is called off)
+    set_variant(c, 2, c->tm_ok ? 3 : persist_form(c) == PS_FREE ? 2 : 0, opf_default_rows(c));
+    c->ps_rows = R;
+    return ADEF2_OK;
+  }
   // fused operator pass: the (tile height, instances per block) candidates
   // the options allow; slot: where a candidate's trial time is reported
   const int64_t ho = opf_halo(c);

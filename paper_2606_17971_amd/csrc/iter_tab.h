@@ -25,6 +25,15 @@ struct KTab {
 template <typename V, typename M, int RPT>
 KTab<V, M> pick_kp(int KP);
 
+// persistent chunk kernel: R rows of one instance per block, form of W^T z as
+// in dev_persist.h; defined in iter_persist.hip for V, M in {(double, double),
+// (double, float), (float, float)} and R in {256, 512, 1024}
+struct PersistArgs;
+template <typename V, typename M>
+using PersistFn = void (*)(IterArgs<V, M>, PersistArgs);
+template <typename V, typename M, int R>
+PersistFn<V, M> pick_persist(int KP, int form);
+
 // tile-major kernels of a basis shared by every instance (FP64 vectors):
 // the W-free pair (pupdate_bt, zproj_bt) and the boundary-form pair
 // (pupdate_tm, update_tm)
