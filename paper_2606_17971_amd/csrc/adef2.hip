@@ -1022,7 +1022,7 @@ int persist_rows(adef2_ctx* c) {
         hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, PS_TB, lds) != hipSuccess)
       return 0;
-    if (blocks <= (int64_t)per * c->n_cu) return R;
+    if (cdiv(blocks, (int64_t)8) <= (int64_t)per * (c->n_cu / 8)) return R;   // blocks of an XCD
   }
   return 0;
 }
@@ -1058,7 +1058,6 @@ void launch_persist(adef2_ctx* c, const IterArgs<V, M>& a, int chunk, hipStream_
   pa.dots = c->ps_dots;
   pa.shake = c->ps_shake;
   pa.nt = (int)cdiv(c->N, (int64_t)c->ps_rows);
-  pa.nt_pad = (int)cdiv(pa.nt, 8) * 8;
   pa.nblk = (unsigned)(pa.nt * c->B);
   pa.seq = ++c->ps_seq;
   pa.base = c->ps_base;
@@ -1067,7 +1066,7 @@ void launch_persist(adef2_ctx* c, const IterArgs<V, M>& a, int chunk, hipStream_
   pa.reach = op_reach(c->offs);
   pa.reach1 = c->factored ? op_reach(c->offs1) : 0;
   pa.fused = persist_fused(c, c->ps_rows);
-  hipLaunchKernelGGL((persist_fn<V, M>(c->KP, c->ps_rows, persist_form(c))), dim3((unsigned)(pa.nt_pad * c->B)),
+  hipLaunchKernelGGL((persist_fn<V, M>(c->KP, c->ps_rows, persist_form(c))), dim3((unsigned)(8 * cdiv(pa.nblk, 8))),
                      dim3(PS_TB), persist_lds(c, c->ps_rows), s, a, pa);
 }
 

@@ -50,7 +50,7 @@ struct PersistArgs {
   unsigned seq;         // number of this launch (from 1)
   unsigned base;        // arrivals before this launch
   unsigned nblk;        // blocks that arrive
-  int nt, nt_pad;       // tiles, and tiles per instance of the grid (multiple of 8)
+  int nt;               // tiles of an instance
   int chunk;            // iterations
   int reach1, reach;    // reach of the inner (factored) and of the outer stencil
   int fused;            // the inner product stays in LDS, its halo formed twice
@@ -63,6 +63,18 @@ __device__ __forceinline__ T ld_agent(const T* p) {
 template <typename T>
 __device__ __forceinline__ void st_agent(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Tile and instance (or group of instances) of this block, n of them per tile,
+// in a grid of 8 * ceil(nt n / 8) blocks (tile >= nt: nothing to do).  Blocks go
+// to the 8 XCDs in turn, each XCD owning a contiguous range of (tile, instance):
+// every XCD then has the same number of blocks to hold, where whole tiles per
+// XCD leave some with more than fit (25 tiles x 20 instances: 80 on an XCD that
+// holds 64) and the launch is called off.
+__device__ __forceinline__ void ps_place(int n, int& tile, int& which) {
+  const int id = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  tile = id / n;
+  which = id - tile * n;
 }
 
 // Poll until *p reaches v (step counters grow); false when the bound passed.
@@ -365,7 +377,7 @@ k_persist(IterArgs<V, M> a, PersistArgs pa) {
   __shared__ short blist[SPEC ? R : 1];
   __shared__ int bcnt[SPEC ? R / 64 + 1 : 1];
   int tile, m;
-  tile_inst(pa.nt_pad, tile, m);
+  ps_place(a.B, tile, m);
   if (tile >= pa.nt) return;
   const int t0_ = threadIdx.x, wid = __builtin_amdgcn_readfirstlane(t0_ >> 6);
   Inst* S = a.inst + m;

@@ -88,3 +88,17 @@ def test_chunk_kernels_of_two_threads(lib):
     for q in range(2):
         assert got[q] is not None
         assert np.linalg.norm(got[q] - ref) <= 1e-8 * np.linalg.norm(ref)
+
+
+def test_chunk_kernel_fills_the_xcds_evenly(lib):
+    """9 tiles x 56 instances, 504 of the 512 places: every XCD gets 63 of its
+    64, so no launch is called off (no kernel of the per-step form runs)."""
+    w = gen.c2_workload(n=91, k=8, B=56)
+    S = spec(w.op, "factored")
+    case("persistent chunk mixed cd2d n=91 k=8 B=56")
+    s = solver(lib, w.op, w.Z, "factored", profile=1, precision=lib.MIXED_REFINE)
+    out = s.solve_batched(np.stack([i.mask for i in w.instances]), np.stack([i.b for i in w.instances]), 1e-10)
+    st = s.stats()
+    assert st["chunk"]["launches"] > 0
+    assert st["update_tm"]["launches"] == 0 and st["pupdate_tm"]["launches"] == 0
+    _check(lib, w, S, out, "mixed", (0, 55), 1e-10)
