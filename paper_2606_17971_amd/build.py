@@ -34,6 +34,8 @@ for v, m, tag in (("double", "double", "dd"), ("double", "float", "df"), ("float
     for r in (256, 512, 1024):
         UNITS.append((f"iter_persist_{tag}_{r}", "iter_persist.hip",
                       [f"-DITER_V={v}", f"-DITER_M={m}", f"-DITER_R={r}"]))
+for e in (8, 16, 20):
+    UNITS.append((f"iter_persist_tm_{e}", "iter_persist_tm.hip", [f"-DITER_E={e}"]))
 UNITS.append(("iter_bt", "iter_bt.hip", []))
 
 

@@ -12,7 +12,7 @@
 
 #include "../../include/adef2.h"
 #include "dev_learned.h"
-#include "dev_persist.h"
+#include "dev_persist_tm.h"
 #include "iter_tab.h"
 
 using namespace adef2;
@@ -227,6 +227,16 @@ struct adef2_ctx {
   unsigned* ps_shake = nullptr;
   size_t ps_tiles = 0, ps_vals = 0;   // tiles, and tiles times values, allocated
   unsigned ps_seq = 0, ps_base = 0;
+  // persistent tile-major chunk kernel (k_persist_tm): steps its registers are
+  // laid out for (0: not in use), steps and rows per tile; rows of 16 instances
+  int pt_e = 0, pt_er = 0, pt_rows = 0, pt_nt = 0;
+  bool pt_fused = false;
+  double *pt_P = nullptr, *pt_T = nullptr, *pt_Q = nullptr, *pt_X = nullptr, *pt_D = nullptr;
+  int64_t pt_N = 0;
+  int pt_H = 0, pt_ng = 0;
+  unsigned* pt_flags = nullptr;
+  double *pt_pw = nullptr, *pt_dots = nullptr, *pt_pub = nullptr;
+  size_t pt_tiles = 0, pt_vals = 0, pt_pubs = 0;
   RedGeom g_iter{};
   int gram_blocks = 0;
   RedGeom g_gram{};
@@ -332,6 +342,7 @@ void free_all(adef2_ctx* c) {
   F(c->t64); F(c->t32); F(c->Tm); F(c->dia1_64); F(c->dia1_32);
   F(c->part); F(c->ctr);
   F(c->ps_flags); F(c->ps_pw); F(c->ps_dots); F(c->ps_shake);
+  F(c->pt_P); F(c->pt_T); F(c->pt_Q); F(c->pt_X); F(c->pt_D); F(c->pt_flags); F(c->pt_pw); F(c->pt_dots); F(c->pt_pub);
   F(c->Phi); F(c->mlp); F(c->mlp_bf); F(c->mlp_g); F(c->mlp_m); F(c->mlp_v); F(c->theta_tr);
   F(c->Htr); F(c->Ntr); F(c->gtr); F(c->e0tr); F(c->bxtr); F(c->act); F(c->mout); F(c->dout); F(c->dA1);
   F(c->dA2); F(c->lossv); F(c->Zb64); F(c->Zb32); F(c->mu64); F(c->eigf); F(c->bnd); F(c->hb); F(c->zero64);
@@ -492,6 +503,7 @@ int opf_default_rows(const adef2_ctx* c) {
 // instances per block
 void set_variant(adef2_ctx* c, int rpt, int wfree, int opf = 0, int opg = 1, int uws = 0) {
   c->ps_rows = 0;
+  c->pt_e = 0;
   c->rpt = rpt;
   c->wfree = wfree;
   c->of_rows = opf;
@@ -964,6 +976,13 @@ PersistFn<V, M> persist_fn(int KP, int rows, int form) {
   }
 }
 
+// compute units of the context's device (0: unknown)
+int device_cus(adef2_ctx* c) {
+  if (!c->n_cu && hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, c->dev) != hipSuccess)
+    c->n_cu = 0;
+  return c->n_cu;
+}
+
 // form of W^T z in the persistent chunk kernel
 int persist_form(const adef2_ctx* c) {
   if (c->KP == 0) return PS_STORED;
@@ -1004,11 +1023,7 @@ int persist_rows(adef2_ctx* c) {
   if (o.w_mode || o.rows_per_thread || o.op_fused || o.op_rows || o.op_group || o.update_ws) return 0;
   // FP32 panels in the boundary form: every column has to be in it
   if (c->ne > 0 && (c->zs != 0 || c->n_eig != c->k)) return 0;
-  if (!c->n_cu) {
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, c->dev) != hipSuccess) return 0;
-    c->n_cu = prop.multiProcessorCount;
-  }
+  if (!device_cus(c)) return 0;
   for (int R : {256, 512, 1024}) {
     const int64_t blocks = cdiv(c->N, (int64_t)R) * c->B;
     if ((R == 256 && blocks > 128) || (R == 512 && blocks > c->n_cu)) continue;
@@ -1027,16 +1042,22 @@ int persist_rows(adef2_ctx* c) {
   return 0;
 }
 
+// words of the handshake
+int persist_shake(adef2_ctx* c) {
+  if (c->ps_shake) return ADEF2_OK;
+  int rc;
+  if ((rc = dalloc(c, &c->ps_shake, PS_WORDS))) return rc;
+  fill<unsigned>(c, c->ps_shake, PS_WORDS, 0u);
+  c->ps_seq = c->ps_base = 0;
+  return ADEF2_OK;
+}
+
 // exchange buffers for the current batch
 int persist_buffers(adef2_ctx* c) {
   const size_t tiles = (size_t)cdiv(c->N, (int64_t)c->ps_rows) * c->B;
   const size_t vals = tiles * (2 * c->KP + 2);
   int rc;
-  if (!c->ps_shake) {
-    if ((rc = dalloc(c, &c->ps_shake, PS_WORDS))) return rc;
-    fill<unsigned>(c, c->ps_shake, PS_WORDS, 0u);
-    c->ps_seq = c->ps_base = 0;
-  }
+  if ((rc = persist_shake(c))) return rc;
   if (tiles > c->ps_tiles) {
     c->ps_tiles = 0;
     if ((rc = dalloc(c, &c->ps_flags, tiles)) || (rc = dalloc(c, &c->ps_pw, 3 * tiles))) return rc;
@@ -1068,6 +1089,139 @@ void launch_persist(adef2_ctx* c, const IterArgs<V, M>& a, int chunk, hipStream_
   pa.fused = persist_fused(c, c->ps_rows);
   hipLaunchKernelGGL((persist_fn<V, M>(c->KP, c->ps_rows, persist_form(c))), dim3((unsigned)(8 * cdiv(pa.nblk, 8))),
                      dim3(PS_TB), persist_lds(c, c->ps_rows), s, a, pa);
+}
+
+// ------------------------------------ persistent tile-major chunk kernel
+PersistTmFn persist_tm_fn(int KP, int E) {
+  switch (E) {
+    case 8: return pick_persist_tm<8>(KP);
+    case 16: return pick_persist_tm<16>(KP);
+    default: return pick_persist_tm<20>(KP);
+  }
+}
+
+size_t persist_tm_lds(const adef2_ctx* c) {
+  const size_t prod = (size_t)PT_NW * 2 * 2 * 256;
+  const size_t t = c->pt_fused ? (size_t)(c->pt_rows + 2 * op_reach(c->offs)) * PT_G : 0;
+  return sizeof(double) * std::max(prod, t);
+}
+
+// Tiles of the persistent tile-major chunk kernel for the current restriction
+// (pt_e > 0 when it applies): one block per compute unit, the rows of a group of
+// 16 instances spread over as many tiles as that leaves.  It is asked for where
+// k_persist does not have every block resident.  Up to 20 steps of rows stay in
+// registers.  Batches under 5 stay with a kernel per step (383^2 x 4, the
+// smallest size at which 4 get here: 70.7 us an iteration, 70.8 here).
+bool persist_tm_plan(adef2_ctx* c) {
+  const adef2_opts& o = c->o;
+  c->pt_e = 0;
+  if (o.w_mode || o.rows_per_thread || o.op_fused || o.op_rows || o.op_group || o.update_ws) return false;
+  if (c->KP == 0 || !c->tm_ok || c->B < 5) return false;
+  const OpGeom og = op_geom(c);
+  if ((og.D != 5 && og.D != 7) || og.d0 != og.D / 2 || (c->factored && (og.D1 != og.D || og.d01 != og.D / 2)))
+    return false;
+  if (!device_cus(c)) return false;
+  const int ng = (int)cdiv(c->B, PT_G);
+  const int most = c->n_cu / ng;
+  if (most < 1) return false;
+  c->pt_er = (int)cdiv(cdiv(c->N, (int64_t)most), (int64_t)PT_STEP);
+  c->pt_rows = PT_STEP * c->pt_er;
+  c->pt_nt = (int)cdiv(c->N, (int64_t)c->pt_rows);
+  int E = 0;
+  for (int e : {8, 16, 20})
+    if (!E && c->pt_er <= e) E = e;
+  if (!E) return false;
+  const void* fn = (const void*)persist_tm_fn(c->KP, E);
+  hipFuncAttributes fa;
+  if (hipFuncGetAttributes(&fa, fn) != hipSuccess) return false;
+  for (int f = c->factored ? 1 : 0; f >= 0; --f) {
+    // A p stays in LDS when its halo fits
+    c->pt_fused = f;
+    const size_t lds = persist_tm_lds(c);
+    int per = 0;
+    if (lds + fa.sharedSizeBytes <= 160 * 1024 && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess &&
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, PT_TB, lds) == hipSuccess && per >= 1) {
+      c->pt_e = E;
+      return true;
+    }
+  }
+  return false;
+}
+
+int persist_tm_buffers(adef2_ctx* c) {
+  const int ng = (int)cdiv(c->B, PT_G);
+  const size_t row = (size_t)(c->N + 2 * c->H) * PT_G, n = row * ng;
+  int rc;
+  if (c->pt_N != c->N || c->pt_H != c->H || c->pt_ng < ng) {
+    // the rows before and after the N of a group stay zero
+    c->pt_N = 0;
+    if ((rc = dalloc(c, &c->pt_P, n))) return rc;
+    for (double** q : {&c->pt_T, &c->pt_Q, &c->pt_X, &c->pt_D})
+      if (*q) { hipFree(*q); *q = nullptr; }
+    fill<double>(c, c->pt_P, n, 0.0);
+    c->pt_N = c->N;
+    c->pt_H = c->H;
+    c->pt_ng = ng;
+  }
+  const size_t na = row * c->pt_ng;
+  if (c->factored && !c->pt_fused && !c->pt_T) {
+    if ((rc = dalloc(c, &c->pt_T, na))) return rc;
+    fill<double>(c, c->pt_T, na, 0.0);
+  }
+  if (!c->pt_Q) {
+    if ((rc = dalloc(c, &c->pt_Q, na))) return rc;
+    fill<double>(c, c->pt_Q, na, 0.0);
+  }
+  if (c->pt_e > 8 && !c->pt_X && (rc = dalloc(c, &c->pt_X, na))) return rc;
+  if (c->pt_e > 16 && !c->pt_D && (rc = dalloc(c, &c->pt_D, na))) return rc;
+  const size_t tiles = (size_t)ng * c->pt_nt, vals = (size_t)c->B * c->pt_nt * (2 * c->KP + 2),
+               pubs = (size_t)ng * PT_G * (c->KP + 3);
+  if (tiles > c->pt_tiles) {
+    c->pt_tiles = 0;
+    if ((rc = dalloc(c, &c->pt_flags, tiles)) || (rc = dalloc(c, &c->pt_pw, 3 * tiles * PT_G))) return rc;
+    c->pt_tiles = tiles;
+  }
+  if (vals > c->pt_vals) {
+    c->pt_vals = 0;
+    if ((rc = dalloc(c, &c->pt_dots, 3 * vals))) return rc;
+    c->pt_vals = vals;
+  }
+  if (pubs > c->pt_pubs) {
+    c->pt_pubs = 0;
+    if ((rc = dalloc(c, &c->pt_pub, 3 * pubs))) return rc;
+    c->pt_pubs = pubs;
+  }
+  return persist_shake(c);
+}
+
+void launch_persist_tm(adef2_ctx* c, const IterArgs<double, float>& a, int chunk, hipStream_t s) {
+  PersistTmArgs pa{};
+  const int64_t halo = (int64_t)c->H * PT_G;
+  pa.flags = c->pt_flags;
+  pa.pw = c->pt_pw;
+  pa.dots = c->pt_dots;
+  pa.pub = c->pt_pub;
+  pa.P = c->pt_P + halo;
+  pa.T = c->pt_T ? c->pt_T + halo : nullptr;
+  pa.Q = c->pt_Q + halo;
+  pa.X = c->pt_X ? c->pt_X + halo : nullptr;
+  pa.D = c->pt_D ? c->pt_D + halo : nullptr;
+  pa.gs = (c->N + 2 * c->H) * PT_G;
+  pa.shake = c->ps_shake;
+  pa.nt = c->pt_nt;
+  pa.ng = (int)cdiv(c->B, PT_G);
+  pa.nblk = (unsigned)(pa.nt * pa.ng);
+  pa.seq = ++c->ps_seq;
+  pa.base = c->ps_base;
+  c->ps_base += pa.nblk;
+  pa.rows = c->pt_rows;
+  pa.er = c->pt_er;
+  pa.chunk = chunk;
+  pa.reach = op_reach(c->offs);
+  pa.reach1 = c->factored ? op_reach(c->offs1) : 0;
+  pa.fused = c->pt_fused;
+  hipLaunchKernelGGL((persist_tm_fn(c->KP, c->pt_e)), dim3((unsigned)(8 * cdiv(pa.nblk, 8))), dim3(PT_TB),
+                     persist_tm_lds(c), s, a, pa);
 }
 
 // max_chunks > 0 stops after that many chunks (tuning trials).
@@ -1142,15 +1296,19 @@ int run_sweep(adef2_ctx* c, const double* src, const double* x0pad, double thres
   const int chunk = std::max(1, c->o.check_every);
   // one chunk of iterations on stream s (kernel arguments are the same for
   // every iteration: all per-iteration state lives in device memory)
-  bool persist = c->ps_rows > 0;
+  bool persist = c->ps_rows > 0 || c->pt_e > 0;
   if (persist) {
-    int rc = persist_buffers(c);
+    int rc = c->pt_e ? persist_tm_buffers(c) : persist_buffers(c);
     if (rc) return rc;
   }
   auto launch_chunk = [&](hipStream_t s) {
     if (persist)
       timed(c, KI_CHUNK, chunk * (bm.pupdate + bm.stencil + bm.spmv + bm.update),
-            [&] { launch_persist<V, M>(c, a, chunk, s); });
+            [&] {
+              if constexpr (sizeof(V) == 8 && sizeof(M) == 4)
+                if (c->pt_e) return launch_persist_tm(c, a, chunk, s);
+              launch_persist<V, M>(c, a, chunk, s);
+            });
     for (int it = 0; it < (persist ? 0 : chunk); ++it) {
       if constexpr (sizeof(V) == 8) {
         if (tm)
@@ -1349,6 +1507,12 @@ int choose_variant(adef2_ctx* c, const double* b) {
     // (the variant of the kernel-per-step form, in case a chunk is called off)
     set_variant(c, 2, c->tm_ok ? 3 : persist_form(c) == PS_FREE ? 2 : 0, opf_default_rows(c));
     c->ps_rows = R;
+    return ADEF2_OK;
+  }
+  if (persist_tm_plan(c)) {
+    const int E = c->pt_e;
+    set_variant(c, 2, 3, opf_default_rows(c));
+    c->pt_e = E;
     return ADEF2_OK;
   }
   // fused operator pass: the (tile height, instances per block) candidates

@@ -301,10 +301,12 @@ __device__ __forceinline__ double ps_gather(const double* slot, int nt, unsigned
   return s;
 }
 
-// One row of a stencil of DC diagonals: coefficients at db[d N + j], sources
-// src(d); the arithmetic and order of stencil_row.
+// One row of a stencil of DC diagonals, the main one in the middle:
+// coefficients at db[d N + j], sources src(d); the arithmetic and order of
+// stencil_row.
 template <int DC, typename M, typename SrcF>
-__device__ __forceinline__ double ps_row(const M* db, int64_t N, unsigned j, int d0, SrcF src) {
+__device__ __forceinline__ double ps_row(const M* db, int64_t N, unsigned j, SrcF src) {
+  constexpr int D0 = DC / 2;
   double vw[DC];
   M cw[DC];
 #pragma unroll
@@ -315,26 +317,19 @@ __device__ __forceinline__ double ps_row(const M* db, int64_t N, unsigned j, int
   __builtin_amdgcn_sched_barrier(0);
   double acc = 0.0;
   if constexpr (sizeof(M) == 4) {
-    if (d0 >= 0) {
-      double vi = 0.0, dg = 0.0;
+    acc = (double)cw[D0] * vw[D0];
 #pragma unroll
-      for (int d = 0; d < DC; ++d)
-        if (d == d0) { vi = vw[d]; dg = (double)cw[d]; }
-      acc = dg * vi;
+    for (int d = 0; d < DC; ++d)
+      if (d != D0) acc += (double)cw[d] * (vw[d] - vw[D0]);
+  } else {
 #pragma unroll
-      for (int d = 0; d < DC; ++d)
-        if (d != d0) acc += (double)cw[d] * (vw[d] - vi);
-      return acc;
-    }
+    for (int d = 0; d < DC; ++d) acc += (double)cw[d] * vw[d];
   }
-#pragma unroll
-  for (int d = 0; d < DC; ++d) acc += (double)cw[d] * vw[d];
   return acc;
 }
+// the same for any number of diagonals
 template <typename M, typename SrcF>
-__device__ __forceinline__ double ps_stencil(const M* db, int64_t N, unsigned j, int D, int d0, SrcF src) {
-  if (D == 5) return ps_row<5>(db, N, j, d0, src);
-  if (D == 7) return ps_row<7>(db, N, j, d0, src);
+__device__ __forceinline__ double ps_row_any(const M* db, int64_t N, unsigned j, int D, int d0, SrcF src) {
   double acc = 0.0;
   if (sizeof(M) == 4 && d0 >= 0) {
     const double vi = src(d0);
@@ -347,6 +342,13 @@ __device__ __forceinline__ double ps_stencil(const M* db, int64_t N, unsigned j,
 #pragma unroll 4
   for (int d = 0; d < D; ++d) acc += (double)(db + (size_t)d * N)[j] * src(d);
   return acc;
+}
+
+template <typename M, typename SrcF>
+__device__ __forceinline__ double ps_stencil(const M* db, int64_t N, unsigned j, int D, int d0, SrcF src) {
+  if (D == 5 && d0 == 2) return ps_row<5>(db, N, j, src);
+  if (D == 7 && d0 == 3) return ps_row<7>(db, N, j, src);
+  return ps_row_any(db, N, j, D, d0, src);
 }
 
 // Forms of W^T z: the stored panel W; SPEC, the boundary form of W (FP32

@@ -34,6 +34,14 @@ using PersistFn = void (*)(IterArgs<V, M>, PersistArgs);
 template <typename V, typename M, int R>
 PersistFn<V, M> pick_persist(int KP, int form);
 
+// persistent tile-major chunk kernel (boundary form of W, modes shared by the
+// batch, FP32 panels with FP64 vectors): E steps of rows in registers; defined
+// in iter_persist_tm.hip for E in {8, 16, 20}
+struct PersistTmArgs;
+using PersistTmFn = void (*)(IterArgs<double, float>, PersistTmArgs);
+template <int E>
+PersistTmFn pick_persist_tm(int KP);
+
 // tile-major kernels of a basis shared by every instance (FP64 vectors):
 // the W-free pair (pupdate_bt, zproj_bt) and the boundary-form pair
 // (pupdate_tm, update_tm)

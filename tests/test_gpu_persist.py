@@ -102,3 +102,48 @@ def test_chunk_kernel_fills_the_xcds_evenly(lib):
     assert st["chunk"]["launches"] > 0
     assert st["update_tm"]["launches"] == 0 and st["pupdate_tm"]["launches"] == 0
     _check(lib, w, S, out, "mixed", (0, 55), 1e-10)
+
+
+def _problem(kind, n, k, B):
+    """(operator, modes, masks, right-hand sides)."""
+    if kind in ("noise", "cube"):
+        # every inactive row has an active neighbour; a 7-point factor
+        op, Z = (gen.c2_operator(n)[0], gen.c2_workload(n=n, k=k, B=1).Z) if kind == "noise" else \
+            (gen.ocp_3d_obstacle(n=n, B=1).op, gen.sine_modes_3d(n, k)[0])
+        rng = np.random.default_rng(n + B)
+        return op, Z, (rng.random((B, op.N)) < 0.25).astype(np.uint8), rng.standard_normal((B, op.N))
+    w = (gen.c3_workload if kind == "het" else gen.c2_workload)(n=n, k=k, B=B)
+    if kind == "het":
+        w.op = gen.Operator(n=n, dim=2, B=gen.c3_operator(n)[1], shift=w.op.shift, name="five-point")
+    return w.op, w.Z, np.stack([i.mask for i in w.instances]), np.stack([i.b for i in w.instances])
+
+
+# batches whose blocks of one instance are not all resident: groups of 16.  A
+# group of 9, 5 steps a tile (8 in registers), last tile short; every row listed
+# (more than LDS holds), 10 steps (16); A p through memory, 18 steps (20), modes
+# in three column tiles; 64 modes; a 7-point factor; a 5-point operator that
+# isn't factored, each instance with its own scale
+@pytest.mark.parametrize("kind,n,k,B", [
+    ("cd", 91, 8, 57), ("noise", 159, 16, 40), ("cd", 191, 40, 64), ("cd", 95, 64, 60), ("cube", 25, 20, 33),
+    ("het", 95, 16, 60)])
+def test_group_chunk_kernel_matches_oracle(lib, kind, n, k, B):
+    op, Z, masks, bs = _problem(kind, n, k, B)
+    form = "assembled" if kind == "het" else "factored"
+    case(f"persistent group chunk mixed {kind} n={n} k={k} B={B}")
+    tol = 1e-8
+    s = solver(lib, op, Z, form, profile=1, precision=lib.MIXED_REFINE)
+    scale = np.linspace(0.5, 2.0, B) if kind == "het" else None
+    out = s.solve_batched(masks, bs, tol, a=scale, c=None if scale is None else op.shift * scale)
+    st = s.stats()
+    assert st["chunk"]["launches"] > 0 and st["update_tm"]["launches"] == 0
+    X = out["x"].cpu().numpy()
+    for m in (0, B // 2, B - 1):
+        # (S_m = a_m S_ref + c_m I, and S_ref holds the shift already)
+        S = spec(op, form) if scale is None else spec(op, form, a=scale[m], c=2 * op.shift * scale[m])
+        ref = oracle.solve_instance(S, Z, masks[m], bs[m], tol)
+        I, xs = _xstar(S, masks[m], bs[m])
+        e, e0 = oracle.rel_err(X[m, I], xs), oracle.rel_err(ref.x[I], xs)
+        print(f"   m={m} iters {out['iters'][m]} (oracle {ref.iters}) e_rel {e:.2e} (oracle {e0:.2e})", flush=True)
+        assert out["status"][m] == 0 and out["relres_true"][m] <= tol
+        assert np.all(X[m, masks[m] == 1] == 0.0)
+        assert e <= max(1e-8, 2 * e0), (m, e)
