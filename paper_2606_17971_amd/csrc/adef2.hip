@@ -966,6 +966,32 @@ int chunk_graph(adef2_ctx* c, const IterArgs<V, M>& a, int chunk, int variant, c
   return ADEF2_OK;
 }
 
+// ------------------------------------------------- symmetric eigenproblems
+// doubles of workspace jacobi_eig needs for an n x n matrix: the rotations, the
+// exchange buffer and the number of rounds
+size_t jacobi_work(int n) {
+  const JacGeom g = jac_geom(n);
+  return (size_t)JSWEEPS * g.rounds * g.np * 2 + 4 * (size_t)g.nblk + 1;
+}
+
+// eigenvalues (unordered) and eigenvectors (V[i * n + j]: entry i of vector j)
+// of the symmetric A, n <= JMAX
+void jacobi_eig(adef2_ctx* c, int n, const double* A, double* V, double* ev, double* work) {
+  const JacGeom g = jac_geom(n);
+  double2* log = (double2*)work;
+  double* xg = work + (size_t)JSWEEPS * g.rounds * g.np * 2;
+  int* nr = (int*)(xg + 4 * (size_t)g.nblk);
+  const size_t rot = (size_t)g.np * sizeof(double2), all = rot + 4 * (size_t)g.nblk * sizeof(double);
+  // blocks per thread, and whether the exchange fits LDS beside the kernel's own
+  // (5050 blocks, n = 200, just do)
+  const bool lds = all + 512 <= 160 * 1024;
+  auto fn = !lds ? k_jacobi_rot<9, false> : g.nblk <= 2 * JTB ? k_jacobi_rot<2, true> : k_jacobi_rot<5, true>;
+  const size_t dyn = lds ? all : rot + (size_t)g.nblk * (sizeof(uint2) + sizeof(int));
+  hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
+  hipLaunchKernelGGL(fn, dim3(1), dim3(JTB), dyn, c->st, n, A, log, nr, xg, ev);
+  hipLaunchKernelGGL(k_jacobi_vecs, dim3((unsigned)cdiv(n, 4)), dim3(256), 0, c->st, n, log, nr, V);
+}
+
 // ------------------------------------------------- persistent chunk kernel
 template <typename V, typename M>
 PersistFn<V, M> persist_fn(int KP, int rows, int form) {
@@ -2394,12 +2420,13 @@ int adef2_reference_eigs(adef2_ctx* c, int32_t r, const double* X0, int32_t max_
   const int rpb = 4096;
   const int nrb = (int)cdiv(N, rpb);
   double *X = nullptr, *Y = nullptr, *Zb = nullptr, *D = nullptr, *part = nullptr, *G = nullptr, *E = nullptr;
-  double *T1 = nullptr, *F = nullptr, *V = nullptr, *ev = nullptr, *T = nullptr, *lam = nullptr, *Gd = nullptr;
+  double *T1 = nullptr, *F = nullptr, *V = nullptr, *ev = nullptr, *T = nullptr, *lam = nullptr, *Gd = nullptr,
+         *jw = nullptr;
   uint8_t* mk = nullptr;
   int* fl = nullptr;
   auto cleanup = [&] {
     for (void* q : {(void*)X, (void*)Y, (void*)Zb, (void*)D, (void*)part, (void*)G, (void*)E, (void*)T1, (void*)F,
-                    (void*)V, (void*)ev, (void*)T, (void*)lam, (void*)Gd, (void*)mk, (void*)fl})
+                    (void*)V, (void*)ev, (void*)T, (void*)lam, (void*)Gd, (void*)jw, (void*)mk, (void*)fl})
       if (q) hipFree(q);
   };
   const size_t NR = (size_t)N * r, RR = (size_t)r * r;
@@ -2408,7 +2435,7 @@ int adef2_reference_eigs(adef2_ctx* c, int32_t r, const double* X0, int32_t max_
       (rc = dalloc(c, &part, (size_t)nrb * RR)) || (rc = dalloc(c, &G, RR)) || (rc = dalloc(c, &E, RR)) ||
       (rc = dalloc(c, &T1, RR)) || (rc = dalloc(c, &F, RR)) || (rc = dalloc(c, &V, RR)) ||
       (rc = dalloc(c, &ev, (size_t)r)) || (rc = dalloc(c, &T, RR)) || (rc = dalloc(c, &lam, (size_t)r)) ||
-      (rc = dalloc(c, &Gd, RR)) || (rc = dalloc(c, &mk, NR)) || (rc = dalloc(c, &fl, 1))) {
+      (rc = dalloc(c, &Gd, RR)) || (rc = dalloc(c, &mk, NR)) || (rc = dalloc(c, &fl, 1)) || (rc = dalloc(c, &jw, jacobi_work(r)))) {
     cleanup();
     return rc;
   }
@@ -2430,7 +2457,7 @@ int adef2_reference_eigs(adef2_ctx* c, int32_t r, const double* X0, int32_t max_
     gram(Y, Y, G);
     gram(Y, X, E);
     hipLaunchKernelGGL(k_rr_reduce, dim3(1), dim3(64), 0, c->st, r, G, E, T1, F, fl);
-    hipLaunchKernelGGL(k_jacobi_eig, dim3(1), dim3(1024), 0, c->st, r, F, V, ev);
+    jacobi_eig(c, r, F, V, ev, jw);
     hipLaunchKernelGGL(k_rr_finish, dim3(1), dim3(64), 0, c->st, r, T1, V, ev, T, lam);
     hipLaunchKernelGGL(k_ritz_vectors, gv, dim3(256), 0, c->st, N, r, T, lam, X, Y, Zb, D);
     gram(D, D, Gd);
@@ -2652,11 +2679,11 @@ int gram_top_eigs(adef2_ctx* c, int M, const double* G, int p, double* V, std::v
   const int L = std::min(M - 1, p + std::max(32, p / 2));
   const size_t ML = (size_t)M * L, LL = (size_t)L * L;
   double *Q = nullptr, *Y = nullptr, *QW = nullptr, *YW = nullptr, *C = nullptr, *U = nullptr, *d = nullptr,
-         *dsc = nullptr, *inv = nullptr, *ths = nullptr, *res = nullptr, *part = nullptr;
+         *dsc = nullptr, *inv = nullptr, *ths = nullptr, *res = nullptr, *part = nullptr, *jw = nullptr;
   int* sel = nullptr;
   auto cleanup = [&] {
     for (void* q : {(void*)Q, (void*)Y, (void*)QW, (void*)YW, (void*)C, (void*)U, (void*)d, (void*)dsc,
-                    (void*)inv, (void*)ths, (void*)res, (void*)part, (void*)sel})
+                    (void*)inv, (void*)ths, (void*)res, (void*)part, (void*)jw, (void*)sel})
       if (q) hipFree(q);
   };
   const int nt = (int)cdiv(L, GT);
@@ -2664,7 +2691,7 @@ int gram_top_eigs(adef2_ctx* c, int M, const double* G, int p, double* V, std::v
   if ((rc = dalloc(c, &Q, ML)) || (rc = dalloc(c, &Y, ML)) || (rc = dalloc(c, &QW, ML)) ||
       (rc = dalloc(c, &YW, ML)) || (rc = dalloc(c, &C, LL)) || (rc = dalloc(c, &U, LL)) ||
       (rc = dalloc(c, &d, (size_t)L)) || (rc = dalloc(c, &dsc, (size_t)L)) || (rc = dalloc(c, &inv, (size_t)L)) ||
-      (rc = dalloc(c, &ths, (size_t)L)) || (rc = dalloc(c, &res, (size_t)L)) || (rc = dalloc(c, &part, LL)) ||
+      (rc = dalloc(c, &ths, (size_t)L)) || (rc = dalloc(c, &res, (size_t)L)) || (rc = dalloc(c, &part, LL)) || (rc = dalloc(c, &jw, jacobi_work(L))) ||
       (rc = dalloc(c, &sel, (size_t)L))) { cleanup(); return rc; }
   const dim3 gcol((unsigned)cdiv(M, 256), (unsigned)L);
   // out = A^T B (L x L, row-major) over the M rows, one row block
@@ -2677,7 +2704,7 @@ int gram_top_eigs(adef2_ctx* c, int M, const double* G, int p, double* V, std::v
   auto svqb = [&](const double* Z, double* Qout) {
     gram(Z, Z, C);
     hipLaunchKernelGGL(k_svqb_scale, dim3(1), dim3(1024), 0, c->st, L, C, dsc);
-    hipLaunchKernelGGL(k_jacobi_eig, dim3(1), dim3(1024), 0, c->st, L, C, U, d);
+    jacobi_eig(c, L, C, U, d, jw);
     hipLaunchKernelGGL(k_svqb_inv, dim3(1), dim3(256), 0, c->st, L, d, 1e-14, inv);
     hipLaunchKernelGGL(k_comb_cols, gcol, dim3(256), 0, c->st, M, L, Z, dsc, U, (const int*)nullptr, inv, Qout);
   };
@@ -2691,7 +2718,7 @@ int gram_top_eigs(adef2_ctx* c, int M, const double* G, int p, double* V, std::v
                        M, L, G, Q, Y);
     gram(Q, Y, C);
     hipLaunchKernelGGL(k_symmetrize, dim3(1), dim3(1024), 0, c->st, L, C);
-    hipLaunchKernelGGL(k_jacobi_eig, dim3(1), dim3(1024), 0, c->st, L, C, U, d);
+    jacobi_eig(c, L, C, U, d, jw);
     hipMemcpyAsync(dh.data(), d, sizeof(double) * L, hipMemcpyDeviceToHost, c->st);
     if (hipStreamSynchronize(c->st) != hipSuccess) { cleanup(); return fail(c, ADEF2_E_HIP, "pod subspace sync"); }
     for (int i = 0; i < L; ++i) idx[i] = i;
@@ -2736,17 +2763,18 @@ int adef2_pod(adef2_ctx* c, int32_t M, const double* X, int32_t p, double* Phi_o
     return fail(c, ADEF2_E_ARG, "need 2 <= M <= 8192 snapshots and 1 <= p < M, p <= 64");
   const int64_t N = c->N;
   const bool direct = M <= JMAX;
-  double *Xc = nullptr, *part = nullptr, *G = nullptr, *V = nullptr, *ev = nullptr;
+  double *Xc = nullptr, *part = nullptr, *G = nullptr, *V = nullptr, *ev = nullptr, *jw = nullptr;
   int* sel = nullptr;
   // at most 16 row blocks of partial Grams (16 M^2 doubles)
   const int rpb = (int)std::max<int64_t>(4096, cdiv(N, 16));
   const int nrb = (int)cdiv(N, rpb);
   const int nt = (int)cdiv(M, GT);
-  auto cleanup = [&] { for (void* q : {(void*)Xc, (void*)part, (void*)G, (void*)V, (void*)ev, (void*)sel}) if (q) hipFree(q); };
+  auto cleanup = [&] { for (void* q : {(void*)Xc, (void*)part, (void*)G, (void*)V, (void*)ev, (void*)jw, (void*)sel}) if (q) hipFree(q); };
   int rc;
   if ((rc = dalloc(c, &Xc, (size_t)N * M)) || (rc = dalloc(c, &part, (size_t)nrb * M * M)) ||
       (rc = dalloc(c, &G, (size_t)M * M)) || (rc = dalloc(c, &V, direct ? (size_t)M * M : (size_t)M * p)) ||
-      (rc = dalloc(c, &ev, direct ? (size_t)M : (size_t)p)) || (rc = dalloc(c, &sel, (size_t)p))) { cleanup(); return rc; }
+      (rc = dalloc(c, &ev, direct ? (size_t)M : (size_t)p)) ||
+      (direct && (rc = dalloc(c, &jw, jacobi_work(M)))) || (rc = dalloc(c, &sel, (size_t)p))) { cleanup(); return rc; }
   hipLaunchKernelGGL(k_center, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, c->st, N, M, X, Xc);
   hipLaunchKernelGGL(k_gram_ts, dim3(nrb, nt * nt, 1), dim3(TPB), 0, c->st, N, M, M, Xc, (int64_t)0, Xc,
                      (int64_t)0, (const uint8_t*)nullptr, (int64_t)0, rpb, part);
@@ -2756,7 +2784,7 @@ int adef2_pod(adef2_ctx* c, int32_t M, const double* X, int32_t p, double* Phi_o
   part = nullptr;
   std::vector<double> th;
   if (direct) {
-    hipLaunchKernelGGL(k_jacobi_eig, dim3(1), dim3(1024), 0, c->st, M, G, V, ev);
+    jacobi_eig(c, M, G, V, ev, jw);
     std::vector<double> evh(M);
     hipMemcpyAsync(evh.data(), ev, sizeof(double) * M, hipMemcpyDeviceToHost, c->st);
     if (hipStreamSynchronize(c->st) != hipSuccess) { cleanup(); return fail(c, ADEF2_E_HIP, "pod sync"); }

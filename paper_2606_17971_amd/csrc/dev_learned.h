@@ -81,88 +81,249 @@ __global__ void k_center(int64_t N, int M, const double* X, double* Xc) {
 }
 
 // ---------------------------------------------------------------------------
-// Cyclic Jacobi eigen-decomposition of a symmetric n x n matrix A (global
-// memory, row-major) with eigenvectors accumulated in V (V[i][j] = entry i of
-// eigenvector j).  One workgroup; parallel round-robin pairs.
+// Cyclic Jacobi eigen-decomposition of a symmetric n x n matrix A (n <= JMAX,
+// row-major): rotations of the n / 2 pairs of a round at once, the pairs of the
+// following rounds by the circle method (the same pairs in the same order for
+// every n: they settle the signs of the vectors).
+//
+// One workgroup.  A stays in registers, a thread holding the 2 x 2 blocks (pair
+// i, pair j), i <= j, of the places tid, tid + 1024, ...; a round rotates every
+// block from both sides and moves the entries to their places of the next round
+// through LDS (through memory when it doesn't fit, n > 200).  The moves are the
+// same in every round, so their addresses are held too.  The rotations are
+// logged for the eigenvectors, whose rows don't depend on each other
+// (k_jacobi_vecs, a wave per row).  Bound: LDS instructions and the serial chain
+// of a rotation.  At n = 200 (rank 64) 6.1 ms and 0.3 ms for the vectors; with A
+// and V in memory, read and written column by column, 346 ms, and 1.2 s where
+// rounding in the null space kept the sweeps going.  n = 256: 50 ms (2.7 s).
 // ---------------------------------------------------------------------------
 constexpr int JMAX = 256;
+constexpr int JSWEEPS = 60;
+constexpr int JTB = 1024;
 
-__global__ void __launch_bounds__(1024) k_jacobi_eig(int n, double* A, double* V, double* evals) {
-  __shared__ double rc[JMAX / 2], rs[JMAX / 2];
-  __shared__ int rp_[JMAX / 2], rq_[JMAX / 2];
-  __shared__ double red[16];
-  const int tid = threadIdx.x, nt = blockDim.x;
-  for (int e = tid; e < n * n; e += nt) V[e] = (e / n == e % n) ? 1.0 : 0.0;
-  __syncthreads();
-  const int M = (n + 1) & ~1;
-  const int npair = M / 2;
-  for (int sweep = 0; sweep < 60; ++sweep) {
+// pairs, rounds of a sweep and 2 x 2 blocks of an n x n matrix
+struct JacGeom {
+  int np, rounds, nblk;
+};
+__host__ __device__ inline JacGeom jac_geom(int n) {
+  const int np = (n + 1) / 2;
+  return JacGeom{np, 2 * np - 1, np * (np + 1) / 2};
+}
+__device__ __forceinline__ int jac_block(int np, int i, int j) {   // i <= j; diagonal blocks first
+  return i == j ? i : np + i * (np - 1) - i * (i - 1) / 2 + (j - i - 1);
+}
+// where the entry at position p (pair p / 2, first or second of it) of the next
+// round is now: the first entries move up, the second ones down, entry 0 stays
+__device__ __forceinline__ int jac_from(int np, int p) {
+  const int i = p >> 1;
+  if (np == 1 || p == 0) return p;
+  if (p & 1) return i == np - 1 ? 2 * i : p + 2;
+  return i == 1 ? 1 : p - 2;
+}
+
+// (p, q) by the rotation (s, h = tan of half the angle): p - s (q + h p) instead
+// of c p - s q, whose c^2 + s^2 is off 1 by a rounding each time
+__device__ __forceinline__ void jac_rotate(const double2& sh, double& p, double& q) {
+  const double p0 = p, q0 = q;
+  p = p0 - sh.x * (q0 + sh.y * p0);
+  q = q0 + sh.x * (p0 - sh.y * q0);
+}
+
+// the index whose entry starts at position p: pair t of round r holds the indices
+// r - t and r + t mod 2 np - 1, pair 0 the last index and r
+__device__ __forceinline__ int jac_index(int np, int p) {
+  return p & 1 ? p >> 1 : 2 * np - 1 - (p >> 1);
+}
+
+// S: blocks per thread; LDSX: the exchange goes through LDS (4 nblk doubles after
+// the np rotations), else through xg, and LDS holds the addresses.  log: [JSWEEPS (2 np - 1)][np] rotations, nrounds: how many
+// rounds were done.
+template <int S, bool LDSX>
+__global__ void __launch_bounds__(JTB) k_jacobi_rot(int n, const double* A, double2* log, int* nrounds, double* xg,
+                                                    double* evals) {
+  extern __shared__ double2 jcs[];
+  __shared__ double red[2][JTB / 64];
+  const JacGeom g = jac_geom(n);
+  const int np = g.np, nblk = g.nblk, tid = threadIdx.x;
+  double* xl = (double*)(jcs + np);                    // LDSX: the exchange;
+  uint2* lfrom = (uint2*)(jcs + np);                   //   else the addresses and pairs of the blocks
+  int* lij = (int*)(lfrom + nblk);
+  double m[S][4];
+  uint2 from[LDSX ? S : 1];
+  int ij[LDSX ? S : 1];
+#pragma unroll
+  for (int u = 0; u < S; ++u) {
+    int e = tid + u * JTB, i = 0, j;
+    if (e >= nblk) e = 0;                              // a copy of block 0, never stored
+    if (e < np) i = j = e;
+    else {
+      e -= np;
+      while (e >= np - 1 - i) e -= np - 1 - i++;
+      j = i + 1 + e;
+    }
+    unsigned at[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      int p = 2 * i + (k >> 1), q = 2 * j + (k & 1);
+      const int lo = min(jac_index(np, p), jac_index(np, q)), hi = max(jac_index(np, p), jac_index(np, q));
+      m[u][k] = hi < n ? A[(size_t)lo * n + hi] : 0.0;
+      p = jac_from(np, p);
+      q = jac_from(np, q);
+      if ((p >> 1) > (q >> 1)) { const int t = p; p = q; q = t; }
+      at[k] = ((p & 1) * 2 + (q & 1)) * nblk + jac_block(np, p >> 1, q >> 1);
+    }
+    const uint2 f{at[0] | at[1] << 16, at[2] | at[3] << 16};
+    if constexpr (LDSX) { from[u] = f; ij[u] = i | j << 16; }
+    else if (tid + u * JTB < nblk) { lfrom[tid + u * JTB] = f; lij[tid + u * JTB] = i | j << 16; }
+  }
+  int done = 0;
+  double prev = INFINITY;
+  for (int sweep = 0; sweep < JSWEEPS; ++sweep) {
     double off = 0.0, dia = 0.0;
-    for (int e = tid; e < n * n; e += nt) {
-      const double v = A[e];
-      if (e / n != e % n) off += v * v; else dia += v * v;
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+      const int e = tid + u * JTB;
+      if (e < np) {
+        off += 2.0 * m[u][1] * m[u][1];
+        dia += m[u][0] * m[u][0] + m[u][3] * m[u][3];
+      } else if (e < nblk) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) off += 2.0 * m[u][k] * m[u][k];
+      }
     }
     off = wave_sum(off);
     dia = wave_sum(dia);
-    if ((tid & 63) == 0) red[tid >> 6] = off;
+    if ((tid & 63) == 0) { red[0][tid >> 6] = off; red[1][tid >> 6] = dia; }
     __syncthreads();
-    double offt = 0.0;
-    for (int w = 0; w < nt / 64; ++w) offt += red[w];
-    __syncthreads();
-    if ((tid & 63) == 0) red[tid >> 6] = dia;
-    __syncthreads();
-    double diat = 0.0;
-    for (int w = 0; w < nt / 64; ++w) diat += red[w];
-    __syncthreads();
-    if (!(offt > 1e-30 * diat)) break;
-    for (int rnd = 0; rnd < M - 1; ++rnd) {
-      for (int t = tid; t < npair; t += nt) {
-        int p, q;
-        if (t == 0) { p = rnd; q = M - 1; }
-        else { p = (rnd + t) % (M - 1); q = (rnd - t + (M - 1)) % (M - 1); }
-        if (p > q) { const int tt = p; p = q; q = tt; }
-        double c = 1.0, s = 0.0;
-        if (q < n) {
-          const double apq = A[p * n + q];
-          if (fabs(apq) > 1e-300) {
-            const double app = A[p * n + p], aqq = A[q * n + q];
-            const double tau = (aqq - app) / (2.0 * apq);
-            const double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-            c = 1.0 / sqrt(1.0 + tt * tt);
-            s = tt * c;
+    off = dia = 0.0;
+    for (int w = 0; w < JTB / 64; ++w) { off += red[0][w]; dia += red[1][w]; }
+    // diagonal, or at rounding level and no longer shrinking (the null space of
+    // a rank-deficient Gram)
+    if (!(off > 1e-30 * dia) || (off <= 1e-27 * dia && off > 0.25 * prev)) break;
+    prev = off;
+    for (int rnd = 0; rnd < g.rounds; ++rnd, ++done) {
+      if (tid < np) {
+        const double apq = m[0][1], app = m[0][0], aqq = m[0][3];
+        double s = 0.0, h = 0.0;
+        if (fabs(apq) > 1e-300) {
+          const double tau = (aqq - app) / (2.0 * apq);
+          // equal diagonal entries: by the order of the indices
+          int i0 = tid ? rnd - tid : g.rounds, i1 = rnd + tid;
+          if (i0 < 0) i0 += g.rounds;
+          if (i1 >= g.rounds) i1 -= g.rounds;
+          const bool pos = i0 < i1 ? tau >= 0.0 : tau > 0.0;
+          const double t = (pos ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
+          const double c = 1.0 / sqrt(1.0 + t * t);
+          s = t * c;
+          h = s / (1.0 + c);
+          m[0][0] = app - t * apq;
+          m[0][3] = aqq + t * apq;
+          m[0][1] = m[0][2] = 0.0;
+        }
+        jcs[tid] = double2{s, h};
+        log[(size_t)done * np + tid] = double2{s, h};
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < S; ++u) {
+        const int e = tid + u * JTB;
+        if (e >= nblk) continue;
+        if (u > 0 || e >= np) {
+          int w;
+          if constexpr (LDSX) w = ij[u]; else w = lij[e];
+          const double2 ci = jcs[w & 0xffff], cj = jcs[w >> 16];
+#pragma unroll
+          for (int k = 0; k < 2; ++k) jac_rotate(ci, m[u][k], m[u][2 + k]);       // rows of pair i
+#pragma unroll
+          for (int k = 0; k < 4; k += 2) jac_rotate(cj, m[u][k], m[u][k + 1]);    // columns of pair j
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if constexpr (LDSX) xl[k * nblk + e] = m[u][k];
+          else xg[k * nblk + e] = m[u][k];
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < S; ++u)
+        if (tid + u * JTB < nblk) {
+          uint2 f;
+          if constexpr (LDSX) f = from[u]; else f = lfrom[tid + u * JTB];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const unsigned at = ((k & 2 ? f.y : f.x) >> (16 * (k & 1))) & 0xffffu;
+            if constexpr (LDSX) m[u][k] = xl[at];
+            else m[u][k] = xg[at];
           }
         }
-        rp_[t] = p; rq_[t] = q; rc[t] = c; rs[t] = s;
-      }
-      __syncthreads();
-      for (int e = tid; e < npair * n; e += nt) {        // A J and V J (columns)
-        const int t = e / n, i = e % n;
-        const int p = rp_[t], q = rq_[t];
-        if (q < n) {
-          const double c = rc[t], s = rs[t];
-          const double aip = A[i * n + p], aiq = A[i * n + q];
-          A[i * n + p] = c * aip - s * aiq;
-          A[i * n + q] = s * aip + c * aiq;
-          const double vip = V[i * n + p], viq = V[i * n + q];
-          V[i * n + p] = c * vip - s * viq;
-          V[i * n + q] = s * vip + c * viq;
-        }
-      }
-      __syncthreads();
-      for (int e = tid; e < npair * n; e += nt) {        // J^T A (rows)
-        const int t = e / n, j = e % n;
-        const int p = rp_[t], q = rq_[t];
-        if (q < n) {
-          const double c = rc[t], s = rs[t];
-          const double apj = A[p * n + j], aqj = A[q * n + j];
-          A[p * n + j] = c * apj - s * aqj;
-          A[q * n + j] = s * apj + c * aqj;
-        }
-      }
-      __syncthreads();
     }
   }
-  for (int i = tid; i < n; i += nt) evals[i] = A[i * n + i];
+  // every sweep ends with the entries at their own places
+  if (tid < np) {
+    const int i0 = jac_index(np, 2 * tid), i1 = jac_index(np, 2 * tid + 1);
+    if (i0 < n) evals[i0] = m[0][0];
+    if (i1 < n) evals[i1] = m[0][3];
+  }
+  if (tid == 0) *nrounds = done;
+}
+
+// lane + 1's / lane - 1's value (0 beyond the wave)
+__device__ __forceinline__ double jac_shift(double v, bool up) {
+  union { double d; int i[2]; } a, b;
+  a.d = v;
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+    b.i[h] = up ? __builtin_amdgcn_update_dpp(0, a.i[h], 0x138, 0xf, 0xf, true)     // wave_shr:1
+                : __builtin_amdgcn_update_dpp(0, a.i[h], 0x130, 0xf, 0xf, true);    // wave_shl:1
+  return b.d;
+}
+
+// Row i of the eigenvectors (V[i][j] = entry i of eigenvector j): row i of the
+// identity through the logged rotations, one wave per row, two pairs per lane.
+__global__ void __launch_bounds__(256) k_jacobi_vecs(int n, const double2* log, const int* nrounds, double* V) {
+  constexpr int PF = 8;                                // rounds whose rotations are loaded together
+  const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (i >= n) return;
+  const int np = jac_geom(n).np, R = *nrounds;
+  const int k0 = min(2 * lane, np - 1), k1 = min(2 * lane + 1, np - 1);
+  double v[4];                                         // pairs 2 lane and 2 lane + 1
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] = jac_index(np, 4 * lane + k) == i && 2 * lane + (k >> 1) < np ? 1.0 : 0.0;
+  double2 cs[2][PF][2];
+  auto load = [&](int r0, double2 (&b)[PF][2]) {
+#pragma unroll
+    for (int q = 0; q < PF; ++q) {
+      const size_t r = (size_t)min(r0 + q, R - 1) * np;
+      b[q][0] = log[r + k0];
+      b[q][1] = log[r + k1];
+    }
+  };
+  auto round = [&](const double2 (&b)[2]) {
+    double t0 = v[0], b0 = v[1], t1 = v[2], b1 = v[3];
+    jac_rotate(b[0], t0, b0);
+    jac_rotate(b[1], t1, b1);
+    if (np == 1) { v[0] = t0; v[1] = b0; return; }
+    const double tl = jac_shift(t1, true), br = jac_shift(b0, false);
+    v[0] = lane == 0 ? t0 : tl;                        // first entries move up, entry 0 stays
+    v[2] = lane == 0 ? b0 : t0;
+    v[1] = 2 * lane == np - 1 ? t0 : b1;               // second entries move down
+    v[3] = 2 * lane + 1 == np - 1 ? t1 : br;
+  };
+  if (R > 0) load(0, cs[0]);
+  for (int r0 = 0; r0 < R; r0 += 2 * PF) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      load(r0 + (h + 1) * PF, cs[(h + 1) & 1]);
+#pragma unroll
+      for (int q = 0; q < PF; ++q)
+        if (r0 + h * PF + q < R) round(cs[h][q]);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int j = jac_index(np, 4 * lane + k);
+    if (2 * lane + (k >> 1) < np && j < n) V[(size_t)i * n + j] = v[k];
+  }
 }
 
 // Phi[:, j] = Xc v_c / sqrt(lambda_c), c = sel[j] (eigenvalue order,
