@@ -118,6 +118,7 @@ struct adef2_ctx {
   float* mlp = nullptr;          // FP32 master parameters (packed)
   uint16_t* mlp_bf = nullptr;    // BF16 compute copy (same layout)
   float* mlp_g = nullptr;        // gradients
+  float* mlp_part = nullptr;     // their sums over slices of the samples
   float* mlp_m = nullptr;        // Adam first moments
   float* mlp_v = nullptr;        // Adam second moments
   int adam_t = 0;
@@ -343,7 +344,7 @@ void free_all(adef2_ctx* c) {
   F(c->part); F(c->ctr);
   F(c->ps_flags); F(c->ps_pw); F(c->ps_dots); F(c->ps_shake);
   F(c->pt_P); F(c->pt_T); F(c->pt_Q); F(c->pt_X); F(c->pt_D); F(c->pt_flags); F(c->pt_pw); F(c->pt_dots); F(c->pt_pub);
-  F(c->Phi); F(c->mlp); F(c->mlp_bf); F(c->mlp_g); F(c->mlp_m); F(c->mlp_v); F(c->theta_tr);
+  F(c->Phi); F(c->mlp); F(c->mlp_bf); F(c->mlp_g); F(c->mlp_part); F(c->mlp_m); F(c->mlp_v); F(c->theta_tr);
   F(c->Htr); F(c->Ntr); F(c->gtr); F(c->e0tr); F(c->bxtr); F(c->act); F(c->mout); F(c->dout); F(c->dA1);
   F(c->dA2); F(c->lossv); F(c->Zb64); F(c->Zb32); F(c->mu64); F(c->eigf); F(c->bnd); F(c->hb); F(c->zero64);
   F(c->ZT32); F(c->bcnt); F(c->ftot); F(c->fctr); F(c->btoff); F(c->btot); F(c->bidx); F(c->bW32);
@@ -1829,14 +1830,14 @@ void mlp_grad_launch(adef2_ctx* c, int M) {
   else
     hipLaunchKernelGGL(k_loss_grad, dim3(M), dim3(512), 0, c->st, M, c->p, c->mout, c->Htr, c->gtr, c->e0tr,
                        c->bxtr, 0.0, 1.0f / (float)M, c->dout, c->lossv);
-  hipLaunchKernelGGL(k_mlp_bwd_act, dim3(M), dim3(128), 0, c->st, M, mlp_view(c), c->act, c->dout,
+  hipLaunchKernelGGL(k_mlp_bwd_act, dim3(M), dim3(512), 0, c->st, M, mlp_view(c), c->act, c->dout,
                      c->dA2, c->dA1);
-  hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)cdiv(MD3 * MD2, 256)), dim3(256), 0, c->st, M, MD3, MD2,
-                     c->dout, MD3, c->act, 4 * MD1, 3 * MD1, c->mlp_g + OW3, c->mlp_g + OB3);
-  hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)cdiv(MD2 * MD1, 256)), dim3(256), 0, c->st, M, MD2, MD1,
-                     c->dA2, MD2, c->act, 4 * MD1, MD1, c->mlp_g + OW2, c->mlp_g + OB2);
-  hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)cdiv(MD1 * MD0, 256)), dim3(256), 0, c->st, M, MD1, MD0,
-                     c->dA1, MD1, c->theta_tr, MD0, 0, c->mlp_g + OW1, c->mlp_g + OB1);
+  const MLPGrad g{c->dout, c->dA2, c->dA1, c->act, c->theta_tr, {OW1, OW2, OW3}, {OB1, OB2, OB3}, NPARAM};
+  // slices of 32 samples, longer ones from 512 samples on
+  const int per = WGS * (int)cdiv(M, WGS * WG_SLICES), slices = (int)cdiv(M, per);
+  hipLaunchKernelGGL(k_mlp_wgrad, dim3(WG3 + WG2 + WG1, slices), dim3(256), 0, c->st, M, per, g, c->mlp_part);
+  hipLaunchKernelGGL(k_mlp_wsum, dim3((unsigned)cdiv(NPARAM, 256)), dim3(256), 0, c->st, NPARAM, slices,
+                     c->mlp_part, c->mlp_g);
 }
 
 // Swaps the shared reference basis for the per-instance enriched basis
@@ -2884,7 +2885,7 @@ int adef2_learned_set_params(adef2_ctx* c, const float* params, double tau_learn
   if (!c->mlp) {
     if ((rc = dalloc(c, &c->mlp, NPARAM)) || (rc = dalloc(c, &c->mlp_bf, NPARAM)) ||
         (rc = dalloc(c, &c->mlp_g, NPARAM)) || (rc = dalloc(c, &c->mlp_m, NPARAM)) ||
-        (rc = dalloc(c, &c->mlp_v, NPARAM)))
+        (rc = dalloc(c, &c->mlp_v, NPARAM)) || (rc = dalloc(c, &c->mlp_part, (size_t)WG_SLICES * NPARAM)))
       return rc;
   }
   HIPCHK(c, hipMemcpyAsync(c->mlp, params, sizeof(float) * NPARAM, hipMemcpyHostToDevice, c->st));

@@ -594,6 +594,23 @@ struct MLPW {            // BF16 compute copies and FP32 biases (device)
   const uint16_t* W3; const float* b3;
 };
 
+// a + row . h, in order; the row is loaded 8 weights at a time (rows of W2 and W3
+// start at multiples of 256 bytes from W1, whose 512 weights and 128 biases come
+// first: 16-byte aligned)
+template <int K>
+__device__ __forceinline__ float mlp_dot(const uint16_t* row, const float* h, float a) {
+  uint4 q[K / 8];
+#pragma unroll
+  for (int k = 0; k < K / 8; ++k) q[k] = ((const uint4*)row)[k];
+#pragma unroll
+  for (int k = 0; k < K / 8; ++k) {
+    const uint32_t w[4] = {q[k].x, q[k].y, q[k].z, q[k].w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) a += bf2f((uint16_t)(w[e >> 1] >> (16 * (e & 1)))) * h[8 * k + e];
+  }
+  return a;
+}
+
 // theta: [B][4]; act: [B][A1 128 | H1 128 | A2 128 | H2 128]; out: [B][512]
 __global__ void __launch_bounds__(512) k_mlp_fwd(int B, const float* theta, MLPW w, float* act, float* out) {
   __shared__ float x0[MD0], h1[MD1], h2[MD2];
@@ -613,7 +630,7 @@ __global__ void __launch_bounds__(512) k_mlp_fwd(int B, const float* theta, MLPW
   __syncthreads();
   if (t < MD2) {
     float a = w.b2[t];
-    for (int k = 0; k < MD1; ++k) a += bf2f(w.W2[t * MD1 + k]) * h1[k];
+    a = mlp_dot<MD1>(w.W2 + t * MD1, h1, a);
     as[2 * MD1 + t] = a;
     h2[t] = gelu_f(a);
     as[3 * MD1 + t] = h2[t];
@@ -621,7 +638,7 @@ __global__ void __launch_bounds__(512) k_mlp_fwd(int B, const float* theta, MLPW
   __syncthreads();
   if (t < MD3) {
     float a = w.b3[t];
-    for (int k = 0; k < MD2; ++k) a += bf2f(w.W3[t * MD2 + k]) * h2[k];
+    a = mlp_dot<MD2>(w.W3 + t * MD2, h2, a);
     out[(size_t)s * MD3 + t] = a;
   }
 }
@@ -810,39 +827,106 @@ __global__ void __launch_bounds__(512) k_loss_grad_spec(int B, int p, const floa
   }
 }
 
-// per-sample backward through the activations: dA2 (128), dA1 (128)
-__global__ void __launch_bounds__(128) k_mlp_bwd_act(int B, MLPW w, const float* act, const float* dout,
+// per-sample backward through the activations: dA2 (128), dA1 (128).  Thread
+// (t, part) sums a quarter of the outputs for input t (512 samples: 9.2 us; 20
+// with one thread per input).
+__global__ void __launch_bounds__(512) k_mlp_bwd_act(int B, MLPW w, const float* act, const float* dout,
                                                      float* dA2, float* dA1) {
-  __shared__ float d2[MD2];
-  const int s = blockIdx.x, t = threadIdx.x;
+  __shared__ float ds[MD3], d2[MD2], part[4][MD2];
+  const int s = blockIdx.x, t = threadIdx.x & 127, h = threadIdx.x >> 7;
   if (s >= B) return;
   const float* as = act + (size_t)s * 4 * MD1;
-  float g = 0.0f;
-  for (int j = 0; j < MD3; ++j) g += dout[(size_t)s * MD3 + j] * bf2f(w.W3[j * MD2 + t]);
-  d2[t] = g * gelu_d(as[2 * MD1 + t]);
-  dA2[(size_t)s * MD2 + t] = d2[t];
+  ds[threadIdx.x] = dout[(size_t)s * MD3 + threadIdx.x];
   __syncthreads();
-  float g1 = 0.0f;
-  for (int j = 0; j < MD2; ++j) g1 += d2[j] * bf2f(w.W2[j * MD1 + t]);
-  dA1[(size_t)s * MD1 + t] = g1 * gelu_d(as[t]);
+  float g = 0.0f;
+#pragma unroll 16
+  for (int j = h * (MD3 / 4); j < (h + 1) * (MD3 / 4); ++j) g += ds[j] * bf2f(w.W3[j * MD2 + t]);
+  part[h][t] = g;
+  __syncthreads();
+  if (h == 0) {
+    d2[t] = ((part[0][t] + part[1][t]) + (part[2][t] + part[3][t])) * gelu_d(as[2 * MD1 + t]);
+    dA2[(size_t)s * MD2 + t] = d2[t];
+  }
+  __syncthreads();
+  g = 0.0f;
+#pragma unroll 16
+  for (int j = h * (MD2 / 4); j < (h + 1) * (MD2 / 4); ++j) g += d2[j] * bf2f(w.W2[j * MD1 + t]);
+  part[h][t] = g;
+  __syncthreads();
+  if (h == 0)
+    dA1[(size_t)s * MD1 + t] = ((part[0][t] + part[1][t]) + (part[2][t] + part[3][t])) * gelu_d(as[t]);
 }
 
-// weight / bias gradients summed over the batch:
+// Weight / bias gradients summed over the batch, all three layers at once:
 //   dW[o][i] = sum_s dA[s][o] X[s][i],  db[o] = sum_s dA[s][o]
-__global__ void k_mlp_wgrad(int B, int nout, int nin, const float* dA, int ldA, const float* X, int ldX,
-                            int offX, float* dW, float* db) {
+// One block per (64 x 64 tile of a layer's weights, slice of the samples): the
+// tile's operands of 32 samples are staged in LDS, 4 x 4 entries per thread;
+// part[slice] holds the sums of a slice in the layout of the parameters, added
+// in order by k_mlp_wsum.  At 512 samples 12 us and 3 us; a thread per weight
+// that walked all samples took 550 us, one load latency per sample.
+struct MLPGrad {
+  const float *dout, *dA2, *dA1, *act, *theta;
+  int ow[3], ob[3], np;    // offsets of the layers' weights and biases, parameters
+};
+constexpr int WGT = 64, WGS = 32;                       // tile edge, samples per step
+constexpr int WG3 = (MD3 / WGT) * (MD2 / WGT), WG2 = (MD2 / WGT) * (MD1 / WGT), WG1 = MD1 / WGT;
+constexpr int WG_SLICES = 16;                           // slices at the most
+
+__global__ void __launch_bounds__(256) k_mlp_wgrad(int B, int per, MLPGrad g, float* part) {
+  __shared__ float as[WGS][WGT], xs[WGS][WGT];
+  int tile = blockIdx.x, nin, ldA, ldX, layer, ntx;
+  const float *A, *X;
+  if (tile < WG3) { layer = 2; nin = MD2; A = g.dout; ldA = MD3; X = g.act + 3 * MD1; ldX = 4 * MD1; ntx = MD2 / WGT; }
+  else if (tile < WG3 + WG2) { tile -= WG3; layer = 1; nin = MD1; A = g.dA2; ldA = MD2; X = g.act + MD1; ldX = 4 * MD1; ntx = MD1 / WGT; }
+  else { tile -= WG3 + WG2; layer = 0; nin = MD0; A = g.dA1; ldA = MD1; X = g.theta; ldX = MD0; ntx = 1; }
+  const int o0 = tile / ntx * WGT, i0 = tile % ntx * WGT;
+  const int t = threadIdx.x, tx = t & 15, ty = t >> 4;
+  float acc[4][4] = {}, ab[4] = {};
+  const int s1 = min(B, ((int)blockIdx.y + 1) * per);
+  for (int s0 = blockIdx.y * per; s0 < s1; s0 += WGS) {
+#pragma unroll
+    for (int u = 0; u < WGS * WGT / 256; ++u) {
+      const int e = t + u * 256, r = e / WGT, c = e % WGT;
+      const bool on = s0 + r < s1;
+      as[r][c] = on ? A[(size_t)(s0 + r) * ldA + o0 + c] : 0.0f;
+      xs[r][c] = on && i0 + c < nin ? X[(size_t)(s0 + r) * ldX + i0 + c] : 0.0f;
+    }
+    __syncthreads();
+#pragma unroll 8
+    for (int r = 0; r < WGS; ++r) {
+      float a[4], x[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) { a[q] = as[r][ty * 4 + q]; x[q] = xs[r][tx * 4 + q]; }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        ab[q] += a[q];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[q][v] += a[q] * x[v];
+      }
+    }
+    __syncthreads();
+  }
+  float* out = part + (size_t)blockIdx.y * g.np;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int o = o0 + ty * 4 + q;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (i0 + tx * 4 + v < nin) out[g.ow[layer] + o * nin + i0 + tx * 4 + v] = acc[q][v];
+    if (tx == 0 && i0 == 0) out[g.ob[layer] + o] = ab[q];
+  }
+}
+
+__global__ void k_mlp_wsum(int n, int slices, const float* part, float* grad) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < nout * nin) {
-    const int o = e / nin, i = e % nin;
-    float s = 0.0f;
-    for (int b = 0; b < B; ++b) s += dA[(size_t)b * ldA + o] * X[(size_t)b * ldX + offX + i];
-    dW[e] = s;
-  }
-  if (e < nout) {
-    float s = 0.0f;
-    for (int b = 0; b < B; ++b) s += dA[(size_t)b * ldA + e];
-    db[e] = s;
-  }
+  if (e >= n) return;
+  float v[WG_SLICES];
+#pragma unroll
+  for (int q = 0; q < WG_SLICES; ++q) v[q] = q < slices ? part[(size_t)q * n + e] : 0.0f;
+  float s = 0.0f;
+#pragma unroll
+  for (int q = 0; q < WG_SLICES; ++q) s += v[q];
+  grad[e] = s;
 }
 
 // Adam (Kingma & Ba 2015) on FP32 master parameters; refreshes the BF16 copy
