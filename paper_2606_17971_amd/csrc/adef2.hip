@@ -417,25 +417,34 @@ void (*accum_fn(int rpt))(OpGeom, const uint8_t*, const V*, double*, int64_t, In
   return k_accumulate<V, 1>;
 }
 
+// T = A Ztilde for the KP columns of B panels
+void launch_stencil_modes(adef2_ctx* c, const OpGeom& og, const double* Z, int64_t zs, const uint8_t* masks, int KP,
+                          int B, double* T) {
+  auto fn = og.D1 == 5 ? k_stencil_modes<5> : og.D1 == 7 ? k_stencil_modes<7> : k_stencil_modes<0>;
+  hipLaunchKernelGGL(fn, dim3((unsigned)cdiv(og.N, (int64_t)TPB), (unsigned)cdiv(KP, SMC), B), dim3(TPB), 0, c->st, og,
+                     c->dia1_64, Z, zs, masks, KP, T);
+}
+
 template <typename V>
 void launch_gram(adef2_ctx* c, const V* dummy_tag, V* W) {
   (void)dummy_tag;
   OpGeom og = op_geom(c);
   dim3 grid(c->gram_blocks, c->B);
   int nsub = 0;
+  decltype(&k_spmm_gram<V, 8, 5>) fn = nullptr;
 #define GRAM_CASE(KPV)                                                                       \
   case KPV:                                                                                  \
     nsub = (int)cdiv(c->N, GramCfg<KPV>::GR);                                                \
-    hipLaunchKernelGGL((k_spmm_gram<V, KPV>), grid, dim3(TPB), 0, c->st, og, c->dia64, c->Z64, \
-                       c->zs, c->Tm, (int)c->factored, c->masks, W, c->inst, c->part, c->ctr,        \
-                       c->g_gram, c->gram, nsub, c->mu64, c->eigf, c->ne);                   \
+    fn = c->D == 5 ? k_spmm_gram<V, KPV, 5> : c->D == 7 ? k_spmm_gram<V, KPV, 7> : k_spmm_gram<V, KPV, 0>; \
     break;
   switch (c->KP) {
     GRAM_CASE(8) GRAM_CASE(16) GRAM_CASE(24) GRAM_CASE(32) GRAM_CASE(40) GRAM_CASE(48)
     GRAM_CASE(56) GRAM_CASE(64)
-    default: break;
+    default: return;
   }
 #undef GRAM_CASE
+  hipLaunchKernelGGL(fn, grid, dim3(TPB), 0, c->st, og, c->dia64, c->Z64, c->zs, c->Tm, (int)c->factored, c->masks, W,
+                     c->inst, c->part, c->ctr, c->g_gram, c->gram, nsub, c->mu64, c->eigf, c->ne);
 }
 
 void launch_coarse(adef2_ctx* c) {
@@ -621,6 +630,13 @@ void fill(adef2_ctx* c, V* p, size_t n, V v) {
   hipLaunchKernelGGL((k_fill<V>), dim3(blocks), dim3(256), 0, c->st, p, (int64_t)n, v);
 }
 
+template <typename V>
+void fill_zero(adef2_ctx* c, const FillList<V>& l, size_t n) {
+  if (l.n == 0 || n == 0) return;
+  hipLaunchKernelGGL((k_fill_zero<V>), dim3((unsigned)std::min<int64_t>(cdiv((int64_t)n, 256), 2048), l.n), dim3(256), 0,
+                     c->st, l, (int64_t)n);
+}
+
 // restrict B instances whose masks are already in c->masks; a, c per instance
 int restrict_batch(adef2_ctx* c, const double* a_h, const double* c_h) {
   const int B = c->B;
@@ -652,20 +668,23 @@ int restrict_batch(adef2_ctx* c, const double* a_h, const double* c_h) {
   // preconditioner and zeroed vectors
   dim3 g1((unsigned)cdiv(N, 256), B);
   const size_t BV = (size_t)B * c->vs;
-  if (c->prec != ADEF2_FP64) fill<double>(c, c->x64, BV, 0.0);
+  FillList<double> zero{};
+  if (c->prec != ADEF2_FP64) zero.add(c->x64);
   if (vec64(c->prec)) {
     hipLaunchKernelGGL((k_dinv<double>), g1, dim3(256), 0, c->st, N, c->diag, c->masks, c->dinv64,
                        c->inst, c->o.precond == ADEF2_NONE);
-    for (int j = 0; j < 5; ++j) fill<double>(c, c->v64[j], BV, 0.0);
+    for (int j = 0; j < 5; ++j) zero.add(c->v64[j]);
   } else {
     hipLaunchKernelGGL((k_dinv<float>), g1, dim3(256), 0, c->st, N, c->diag, c->masks, c->dinv32,
                        c->inst, c->o.precond == ADEF2_NONE);
-    for (int j = 0; j < 5; ++j) fill<float>(c, c->v32[j], BV, 0.0f);
-    fill<double>(c, c->x64, BV, 0.0);
-    fill<float>(c, c->t32, BV, 0.0f);
+    FillList<float> zero32{};
+    for (int j = 0; j < 5; ++j) zero32.add(c->v32[j]);
+    zero32.add(c->t32);
+    fill_zero(c, zero32, BV);
   }
-  fill<double>(c, c->x0pad, BV, 0.0);
-  fill<double>(c, c->t64, BV, 0.0);
+  zero.add(c->x0pad);
+  zero.add(c->t64);
+  fill_zero(c, zero, BV);
   // boundary form of W: FP32 panels and reference modes that are eigenvectors
   // (w_boundary 1: the eigen columns; 2: only when every shared reference
   // mode is one, which also enables the tile-major boundary-form update)
@@ -687,8 +706,7 @@ int restrict_batch(adef2_ctx* c, const double* a_h, const double* c_h) {
     const double wbytes = (mat64(c->prec) ? 8.0 : 4.0);
     timed(c, KI_GRAM, (double)B * N * (c->D * 8.0 + c->KP * (8.0 + wbytes) + 1.0), [&] {
       if (c->factored) {
-        hipLaunchKernelGGL(k_stencil_modes, dim3((unsigned)cdiv(N, 256), c->KP, B), dim3(256), 0,
-                           c->st, op_geom(c), c->dia1_64, c->Z64, c->zs, c->masks, c->KP, c->Tm);
+        launch_stencil_modes(c, op_geom(c), c->Z64, c->zs, c->masks, c->KP, B, c->Tm);
       }
       if (mat64(c->prec)) launch_gram<double>(c, nullptr, c->W64);
       else launch_gram<float>(c, nullptr, c->W32);
@@ -2963,8 +2981,7 @@ int adef2_learned_prepare(adef2_ctx* c, int32_t M, const uint8_t* masks, const d
     ih.c = ua * c->shift_ref + uc;
     hipMemcpyAsync(one, &ih, sizeof(Inst), hipMemcpyHostToDevice, c->st);
     // S_II [Z | Phi] restricted: T = A Vtilde on all rows, W = a A^T T + c Vtilde (inactive rows)
-    hipLaunchKernelGGL(k_stencil_modes, dim3((unsigned)cdiv(N, 256), nb, 1), dim3(256), 0, c->st, og,
-                       c->dia1_64, VB, (int64_t)0, mk, nb, T);
+    launch_stencil_modes(c, og, VB, 0, mk, nb, 1, T);
     hipLaunchKernelGGL(k_outer_cols, dim3((unsigned)cdiv(N, 256), nb), dim3(256), 0, c->st, og, c->dia64,
                        T, VB, mk, one, Wv);
     hipLaunchKernelGGL(k_gram_ts, dim3(nrb, nt * nt, 1), dim3(TPB), 0, c->st, N, nb, nb, VB, (int64_t)0,

@@ -139,8 +139,14 @@ __device__ inline bool tree_reduce(const RedGeom& g, int tile, int nv, double* p
                                              __HIP_MEMORY_SCOPE_AGENT);
     const bool top = (l == g.nlev - 1);
     for (int j = threadIdx.x; j < nv; j += blockDim.x) {
-      double s = 0.0;
-      for (int i = 0; i < cnt; ++i) s += ld_coherent(&part[(size_t)(g.pofs[l - 1] + first + i) * nv + j]);
+      // all children are loaded before the first is added
+      double v[RED_FAN], s = 0.0;
+#pragma unroll
+      for (int i = 0; i < RED_FAN; ++i)
+        v[i] = ld_coherent(&part[(size_t)(g.pofs[l - 1] + first + (i < cnt ? i : 0)) * nv + j]);
+#pragma unroll
+      for (int i = 0; i < RED_FAN; ++i)
+        if (i < cnt) s += v[i];
       if (top) out[j] = s;
       else st_coherent(&part[(size_t)(g.pofs[l] + parent) * nv + j], s);
     }

@@ -191,22 +191,59 @@ __global__ void k_dia_transpose(OpGeom op, const double* A64, double* AT64, floa
 }
 
 // T[m][q] = A Ztilde[q] on all rows, Ztilde = Z with the active rows of
-// instance m set to zero (factored operator, setup of W).
-__global__ void k_stencil_modes(OpGeom op, const double* A64, const double* Z64, int64_t zs,
-                                const uint8_t* mask, int KP, double* T) {
-  const int q = blockIdx.y;
+// instance m set to zero (factored operator, setup of W).  SMC columns per
+// thread share the coefficients and the mask, and their loads are in flight
+// together; DC: diagonals of A, 0 for any (one load at a time).  Bound by
+// reading Z and writing T: 511^2, k = 32: 87 us with a column per thread,
+// 55 us now.
+constexpr int SMC = 4;
+template <int DC>
+__global__ void __launch_bounds__(TPB) k_stencil_modes(OpGeom op, const double* A64, const double* Z64, int64_t zs,
+                                                       const uint8_t* mask, int KP, double* T) {
+  const int q0 = blockIdx.y * SMC;
   const int m = blockIdx.z;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t N = op.N;
   if (i >= N) return;
   const uint8_t* mk = mask + (size_t)m * N;
-  const double* Zq = Z64 + (size_t)m * zs + (size_t)q * N;
-  double acc = 0.0;
-  for (int e = 0; e < op.D1; ++e) {
-    const int64_t j = i + op.offs1[e];
-    if (j >= 0 && j < N && mk[j] == 0) acc += A64[(size_t)e * N + i] * Zq[j];
+  const double* Zq = Z64 + (size_t)m * zs + (size_t)q0 * N;
+  const int nc = min(SMC, KP - q0);                    // columns of this thread (KP: of the panel)
+  double acc[SMC];
+#pragma unroll
+  for (int c = 0; c < SMC; ++c) acc[c] = 0.0;
+  if constexpr (DC > 0) {
+    double cw[DC], v[SMC][DC];
+    int jo[DC];
+    bool in[DC];
+#pragma unroll
+    for (int e = 0; e < DC; ++e) {
+      const int64_t j = i + op.offs1[e];
+      in[e] = j >= 0 && j < N;
+      jo[e] = in[e] ? op.offs1[e] : 0;
+      in[e] = in[e] && mk[i + jo[e]] == 0;
+      cw[e] = A64[(size_t)e * N + i];
+    }
+#pragma unroll
+    for (int c = 0; c < SMC; ++c)
+#pragma unroll
+      for (int e = 0; e < DC; ++e) v[c][e] = Zq[(size_t)min(c, nc - 1) * N + i + jo[e]];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int c = 0; c < SMC; ++c)
+#pragma unroll
+      for (int e = 0; e < DC; ++e)
+        if (in[e]) acc[c] += cw[e] * v[c][e];
+  } else {
+    for (int e = 0; e < op.D1; ++e) {
+      const int64_t j = i + op.offs1[e];
+      if (j >= 0 && j < N && mk[j] == 0)
+#pragma unroll
+        for (int c = 0; c < SMC; ++c) acc[c] += A64[(size_t)e * N + i] * Zq[(size_t)min(c, nc - 1) * N + j];
+    }
   }
-  T[((size_t)m * KP + q) * N + i] = acc;
+#pragma unroll
+  for (int c = 0; c < SMC; ++c)
+    if (c < nc) T[((size_t)m * KP + q0 + c) * N + i] = acc[c];
 }
 
 // ---------------------------------------------------------------------------
@@ -658,15 +695,24 @@ __global__ void __launch_bounds__(UB_ROWS) k_bnd_fill(int64_t N, int ntiles, int
 template <int KP> struct GramCfg {
   static constexpr int GR = KP > 32 ? 32 : 64;                 // rows per sub-tile
   static constexpr int NOUT = 2 * KP * KP;
-  static constexpr int OPT = (NOUT + TPB - 1) / TPB;           // outputs per thread
   static constexpr int CG = TPB / GR;                          // column groups
   static constexpr int CPG = (KP + CG - 1) / CG;               // columns per group
-  static constexpr int LDS = (2 * GR * KP > NOUT ? 2 * GR * KP : NOUT);
+  static constexpr int NT = (KP + 15) / 16;                    // 16-column tiles
+  // row stride: an odd multiple of 16 doubles, so that the four rows of a
+  // matrix-core operand spread over all LDS banks
+  static constexpr int LD = 16 * (NT | 1);
+  static constexpr int OPW = (2 * NT * NT + NWAVE - 1) / NWAVE; // product tiles per wave
+  static constexpr int LDS = (2 * GR * LD > NOUT ? 2 * GR * LD : NOUT);
 };
 
 // src: stencil source columns, Z itself (assembled operator; read masked) or
-// T = A Ztilde of this instance (factored operator; read unmasked).
-template <typename V, int KP>
+// T = A Ztilde of this instance (factored operator; read unmasked).  DC: number
+// of diagonals of the operator, 0 for any (then one load at a time).
+// Bound: reading Z and T and writing W.  The products run on the FP64 matrix
+// cores, each wave taking whole 16 x 16 tiles; all loads of a thread's columns
+// are in flight together.  511^2, k = 32: 422 us with products from LDS and one
+// load at a time, 107 us now.
+template <typename V, int KP, int DC>
 __global__ void __launch_bounds__(TPB) k_spmm_gram(OpGeom op, const double* dia64, const double* Z64,
                                                     int64_t zs, const double* src, int factored,
                                                     const uint8_t* mask, V* W, Inst* inst,
@@ -674,70 +720,116 @@ __global__ void __launch_bounds__(TPB) k_spmm_gram(OpGeom op, const double* dia6
                                                     double* gram, int nsub, const double* mu,
                                                     const uint8_t* eig, int ne) {
   using C = GramCfg<KP>;
+  typedef double d4 __attribute__((ext_vector_type(4)));
   __shared__ double lds[C::LDS];
-  double* zt = lds;                 // [GR][KP]
-  double* wt = lds + C::GR * KP;    // [GR][KP]
+  double* zt = lds;                 // [GR][LD]
+  double* wt = lds + C::GR * C::LD; // [GR][LD]
   const int m = blockIdx.y;
   const Inst* S = inst + m;
   const int64_t N = op.N;
   const uint8_t* mk = mask + (size_t)m * N;
   V* Wm = W + (size_t)m * KP * N;
+  const double* Zm = Z64 + (size_t)m * zs;
+  const double* src0 = factored ? src + (size_t)m * KP * N : Zm;
   const double sa = S->a, sc = S->c;
-  double acc[C::OPT];
+  d4 acc[C::OPW];
 #pragma unroll
-  for (int o = 0; o < C::OPT; ++o) acc[o] = 0.0;
+  for (int o = 0; o < C::OPW; ++o) acc[o] = d4{0.0, 0.0, 0.0, 0.0};
   const int row = threadIdx.x % C::GR;
   const int cg = threadIdx.x / C::GR;
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  // columns KP .. 16 NT stay zero
+  if (C::NT * 16 > KP)
+    for (int e = threadIdx.x; e < 2 * C::GR * C::LD; e += TPB) lds[e] = 0.0;
+  __syncthreads();
   for (int st = blockIdx.x; st < nsub; st += gridDim.x) {
     const int64_t i = (int64_t)st * C::GR + row;
     const bool act = (i >= N) || mk[i] != 0;
+    double zv[C::CPG], sv[C::CPG];
+#pragma unroll
+    for (int cc = 0; cc < C::CPG; ++cc) zv[cc] = sv[cc] = 0.0;
+    if (!act) {
+      if constexpr (DC > 0) {
+        double cw[DC], v[C::CPG][DC];
+        int jo[DC];
+        bool in[DC];
+#pragma unroll
+        for (int d = 0; d < DC; ++d) {
+          const int64_t j = i + op.offs[d];
+          in[d] = j >= 0 && j < N;
+          jo[d] = in[d] ? op.offs[d] : 0;
+          in[d] = in[d] && (factored || mk[i + jo[d]] == 0);
+          cw[d] = dia64[(size_t)d * N + i];
+        }
+#pragma unroll
+        for (int cc = 0; cc < C::CPG; ++cc) {
+          const int q = min(cg * C::CPG + cc, KP - 1);
+          zv[cc] = Zm[(size_t)q * N + i];
+#pragma unroll
+          for (int d = 0; d < DC; ++d) v[cc][d] = src0[(size_t)q * N + i + jo[d]];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int cc = 0; cc < C::CPG; ++cc)
+#pragma unroll
+          for (int d = 0; d < DC; ++d)
+            if (in[d]) sv[cc] += cw[d] * v[cc][d];
+      } else {
+        for (int cc = 0; cc < C::CPG; ++cc) {
+          const int q = cg * C::CPG + cc;
+          if (q >= KP) break;
+          double s = 0.0;
+          for (int d = 0; d < op.D; ++d) {
+            const int64_t j = i + op.offs[d];
+            if (j >= 0 && j < N && (factored || mk[j] == 0))
+              s += dia64[(size_t)d * N + i] * src0[(size_t)q * N + j];
+          }
+          sv[cc] = s;
+          zv[cc] = Zm[(size_t)q * N + i];
+        }
+      }
+    }
 #pragma unroll
     for (int cc = 0; cc < C::CPG; ++cc) {
       const int q = cg * C::CPG + cc;
       if (q < KP) {
-        double wv = 0.0, zv = 0.0;
-        if (!act) {
-          const double* Zq = Z64 + (size_t)m * zs + (size_t)q * N;
-          const double* Sq = factored ? src + ((size_t)m * KP + q) * N : Zq;
-          double s = 0.0;
-          for (int d = 0; d < op.D; ++d) {
-            const int64_t j = i + op.offs[d];
-            if (j >= 0 && j < N && (factored || mk[j] == 0)) s += dia64[(size_t)d * N + i] * Sq[j];
-          }
-          zv = Zq[i];
-          wv = sa * s + sc * zv;
-          // eigen columns are stored as W - lambda Z (zero away from the
-          // active-set boundary up to the eigen-residual); E uses W itself
-          const double lam = (q < ne && eig[q]) ? sa * mu[q] + sc : 0.0;
-          Wm[(size_t)q * N + i] = (V)(wv - lam * zv);
-        } else if (i < N) {
-          Wm[(size_t)q * N + i] = (V)0;
-        }
-        zt[row * KP + q] = zv;
-        wt[row * KP + q] = wv;
+        const double wv = sa * sv[cc] + sc * zv[cc];
+        // eigen columns are stored as W - lambda Z (zero away from the
+        // active-set boundary up to the eigen-residual); E uses W itself
+        const double lam = (q < ne && eig[q]) ? sa * mu[q] + sc : 0.0;
+        if (i < N) Wm[(size_t)q * N + i] = act ? (V)0 : (V)(wv - lam * zv[cc]);
+        zt[row * C::LD + q] = act ? 0.0 : zv[cc];
+        wt[row * C::LD + q] = act ? 0.0 : wv;
       }
     }
     __syncthreads();
+    // product tile o: Z^T Z (o < NT^2) or Z^T W; rows 4 r + lane / 16
 #pragma unroll
-    for (int o = 0; o < C::OPT; ++o) {
-      const int idx = threadIdx.x + o * TPB;
-      if (idx < C::NOUT) {
-        const bool isE = idx >= KP * KP;
-        const int e = isE ? idx - KP * KP : idx;
-        const int jr = e / KP, jc = e % KP;
-        const double* rhs = isE ? wt : zt;
-        double s = 0.0;
-        for (int r2 = 0; r2 < C::GR; ++r2) s += zt[r2 * KP + jr] * rhs[r2 * KP + jc];
-        acc[o] += s;
+    for (int u = 0; u < C::OPW; ++u) {
+      const int o = wid + u * NWAVE;
+      if (o < 2 * C::NT * C::NT) {
+        const int e = o % (C::NT * C::NT), ti = e / C::NT, tj = e % C::NT;
+        const double* za = zt + (lane >> 4) * C::LD + ti * 16 + (lane & 15);
+        const double* xb = (o < C::NT * C::NT ? zt : wt) + (lane >> 4) * C::LD + tj * 16 + (lane & 15);
+#pragma unroll
+        for (int r = 0; r < C::GR / 4; ++r)
+          acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(za[4 * r * C::LD], xb[4 * r * C::LD], acc[u], 0, 0, 0);
       }
     }
     __syncthreads();
   }
-  // block partial: each output owned by exactly one thread
+  // block partial: each output owned by exactly one wave
 #pragma unroll
-  for (int o = 0; o < C::OPT; ++o) {
-    const int idx = threadIdx.x + o * TPB;
-    if (idx < C::NOUT) lds[idx] = acc[o];
+  for (int u = 0; u < C::OPW; ++u) {
+    const int o = wid + u * NWAVE;
+    if (o < 2 * C::NT * C::NT) {
+      const int e = o % (C::NT * C::NT), ti = e / C::NT, tj = e % C::NT;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int jr = ti * 16 + 4 * q + (lane >> 4), jc = tj * 16 + (lane & 15);
+        if (jr < KP && jc < KP) lds[(o < C::NT * C::NT ? 0 : KP * KP) + jr * KP + jc] = acc[u][q];
+      }
+    }
   }
   __syncthreads();
   double* pm = part + (size_t)m * g.ptotal * C::NOUT;
@@ -775,20 +867,28 @@ struct CoarseArgs {
 // Cyclic Jacobi on the leading n x n block of the symmetric matrix A (LDS,
 // row stride KP) in parallel round-robin order; V (LDS, may be null)
 // accumulates the rotations (V <- V J).  On return diag(A) holds the
-// eigenvalues.  Every thread of the block calls it with the same n.
+// eigenvalues.  Every thread of the block calls it with the same n.  A round
+// rotates the 2 x 2 blocks (pair, pair) from both sides in one pass: one thread
+// per block and no index division; bound by the serial chain of a rotation and
+// two barriers.  k_coarse at k = 32: 551 us with a pass over the columns and one
+// over the rows, 247 us now (and its short sums unrolled).
 template <int KP>
 __device__ void jacobi_eig(double* A, double* V, int n, double* rc, double* rs, int* rp_, int* rq_,
                            double* red) {
+  constexpr int PW = KP <= 8 ? 4 : KP <= 16 ? 8 : KP <= 32 ? 16 : 32;   // pairs at the most, to a power of 2
   const int tid = threadIdx.x;
   const int M = (n + 1) & ~1;
   const int npair = M / 2;
+  const int t2 = tid % PW, t10 = tid / PW;
   for (int sweep = 0; sweep < 60; ++sweep) {
     // off-diagonal mass
     double off = 0.0, dia = 0.0;
-    for (int e = tid; e < n * n; e += TPB) {
-      const int aa = e / n, bb = e % n;
-      const double v = A[aa * KP + bb];
-      if (aa != bb) off += v * v; else dia += v * v;
+    for (int e = tid; e < KP * KP; e += TPB) {
+      const int aa = e / KP, bb = e % KP;
+      if (aa < n && bb < n) {
+        const double v = A[e];
+        if (aa != bb) off += v * v; else dia += v * v;
+      }
     }
     off = wave_sum(off);
     dia = wave_sum(dia);
@@ -804,10 +904,11 @@ __device__ void jacobi_eig(double* A, double* V, int n, double* rc, double* rs, 
     __syncthreads();
     if (!(offt > 1e-30 * diat)) break;
     for (int rnd = 0; rnd < M - 1; ++rnd) {
-      for (int t = tid; t < npair; t += TPB) {
-        int p, q;
-        if (t == 0) { p = rnd; q = M - 1; }
-        else { p = (rnd + t) % (M - 1); q = (rnd - t + (M - 1)) % (M - 1); }
+      if (tid < npair) {
+        int p = rnd + tid, q = rnd - tid;
+        if (p >= M - 1) p -= M - 1;
+        if (q < 0) q += M - 1;
+        if (tid == 0) q = M - 1;
         if (p > q) { const int tt = p; p = q; q = tt; }
         double c = 1.0, s = 0.0;
         if (q < n) {
@@ -820,34 +921,32 @@ __device__ void jacobi_eig(double* A, double* V, int n, double* rc, double* rs, 
             s = tt * c;
           }
         }
-        rp_[t] = p; rq_[t] = q; rc[t] = c; rs[t] = s;
+        rp_[tid] = p; rq_[tid] = q; rc[tid] = c; rs[tid] = s;
       }
       __syncthreads();
-      for (int e = tid; e < npair * n; e += TPB) {      // A <- A J (columns)
-        const int t = e / n, i = e % n;
-        const int p = rp_[t], q = rq_[t];
-        if (q < n) {
-          const double c = rc[t], s = rs[t];
-          const double aip = A[i * KP + p], aiq = A[i * KP + q];
-          A[i * KP + p] = c * aip - s * aiq;
-          A[i * KP + q] = s * aip + c * aiq;
-          if (V) {                                        // V <- V J
-            const double vip = V[i * KP + p], viq = V[i * KP + q];
-            V[i * KP + p] = c * vip - s * viq;
-            V[i * KP + q] = s * vip + c * viq;
+      if (t2 < npair) {
+        const int p2 = rp_[t2], q2 = rq_[t2];
+        const double c2 = rc[t2], s2 = rs[t2];
+        const bool h2 = q2 < n;                          // (the last pair of an odd n has one index)
+        for (int t1 = t10; t1 < npair; t1 += TPB / PW) {
+          const int p1 = rp_[t1], q1 = rq_[t1];
+          const double c1 = rc[t1], s1 = rs[t1];
+          const bool h1 = q1 < n;
+          double pp = A[p1 * KP + p2], pq = h2 ? A[p1 * KP + q2] : 0.0;
+          double qp = h1 ? A[q1 * KP + p2] : 0.0, qq = h1 && h2 ? A[q1 * KP + q2] : 0.0;
+          const double ap = c2 * pp - s2 * pq, aq = s2 * pp + c2 * pq;    // A J
+          const double bp = c2 * qp - s2 * qq, bq = s2 * qp + c2 * qq;
+          A[p1 * KP + p2] = c1 * ap - s1 * bp;                            // J^T (A J)
+          if (h1) A[q1 * KP + p2] = s1 * ap + c1 * bp;
+          if (h2) A[p1 * KP + q2] = c1 * aq - s1 * bq;
+          if (h1 && h2) A[q1 * KP + q2] = s1 * aq + c1 * bq;
+        }
+        if (V && h2)
+          for (int i = t10; i < n; i += TPB / PW) {                       // V <- V J
+            const double vip = V[i * KP + p2], viq = V[i * KP + q2];
+            V[i * KP + p2] = c2 * vip - s2 * viq;
+            V[i * KP + q2] = s2 * vip + c2 * viq;
           }
-        }
-      }
-      __syncthreads();
-      for (int e = tid; e < npair * n; e += TPB) {      // A <- J^T A (rows)
-        const int t = e / n, j = e % n;
-        const int p = rp_[t], q = rq_[t];
-        if (q < n) {
-          const double c = rc[t], s = rs[t];
-          const double apj = A[p * KP + j], aqj = A[q * KP + j];
-          A[p * KP + j] = c * apj - s * aqj;
-          A[q * KP + j] = s * apj + c * aqj;
-        }
       }
       __syncthreads();
     }
@@ -910,10 +1009,9 @@ __global__ void __launch_bounds__(TPB) k_coarse(CoarseArgs ca) {
       for (int l = j + 1 + tid; l < k; l += TPB) A0[j * KP + l] /= rjj;
       if (tid == 0) A0[j * KP + j] = rjj;
       __syncthreads();
-      const int rem = k - j - 1;
-      for (int e = tid; e < rem * rem; e += TPB) {
-        const int l = j + 1 + e / rem, mm = j + 1 + e % rem;
-        if (mm >= l) A0[l * KP + mm] -= A0[j * KP + l] * A0[j * KP + mm];
+      for (int e = (j + 1) * KP + tid; e < k * KP; e += TPB) {
+        const int l = e / KP, mm = e % KP;
+        if (mm >= l && mm < k) A0[e] -= A0[j * KP + l] * A0[j * KP + mm];
       }
       ++kp;
     } else {
@@ -935,6 +1033,7 @@ __global__ void __launch_bounds__(TPB) k_coarse(CoarseArgs ca) {
     A1[c * KP + c] = 1.0 / A0[c * KP + c];
     for (int i = c - 1; i >= 0; --i) {
       double s = 0.0;
+#pragma unroll 8
       for (int mm = i + 1; mm <= c; ++mm) s += A0[i * KP + mm] * A1[mm * KP + c];
       A1[i * KP + c] = -s / A0[i * KP + i];
     }
@@ -949,6 +1048,7 @@ __global__ void __launch_bounds__(TPB) k_coarse(CoarseArgs ca) {
   for (int e = tid; e < kp * kp; e += TPB) {
     const int aa = e / kp, bb = e % kp;
     double s = 0.0;
+#pragma unroll 8
     for (int mm = 0; mm <= bb; ++mm) s += A2[aa * KP + mm] * A1[mm * KP + bb];
     A0[aa * KP + bb] = s;
   }
@@ -956,6 +1056,7 @@ __global__ void __launch_bounds__(TPB) k_coarse(CoarseArgs ca) {
   for (int e = tid; e < kp * kp; e += TPB) {
     const int aa = e / kp, bb = e % kp;
     double s = 0.0;
+#pragma unroll 8
     for (int mm = 0; mm <= aa; ++mm) s += A1[mm * KP + aa] * A0[mm * KP + bb];
     A2[aa * KP + bb] = s;
   }
@@ -1054,10 +1155,9 @@ __global__ void __launch_bounds__(TPB) k_coarse(CoarseArgs ca) {
     for (int l = j + 1 + tid; l < kp; l += TPB) A2[l * KP + j] /= ljj;
     if (tid == 0) A2[j * KP + j] = ljj;
     __syncthreads();
-    const int rem = kp - j - 1;
-    for (int e = tid; e < rem * rem; e += TPB) {
-      const int l = j + 1 + e / rem, mm = j + 1 + e % rem;
-      if (mm <= l) A2[l * KP + mm] -= A2[l * KP + j] * A2[mm * KP + j];
+    for (int e = (j + 1) * KP + tid; e < kp * KP; e += TPB) {
+      const int l = e / KP, mm = e % KP;
+      if (mm > j && mm <= l) A2[e] -= A2[l * KP + j] * A2[mm * KP + j];
     }
     __syncthreads();
   }
@@ -1075,6 +1175,7 @@ __global__ void __launch_bounds__(TPB) k_coarse(CoarseArgs ca) {
       const int i = e / kp, c = e % kp;
       const int col = ord[i];
       double s = 0.0;
+#pragma unroll 8
       for (int mm = c; mm < kp; ++mm) s += A2[mm * KP + col] * A1[c * KP + mm];
       A0[i * KP + c] = s / sqrt(gdiag[i]);
     }
@@ -1082,6 +1183,7 @@ __global__ void __launch_bounds__(TPB) k_coarse(CoarseArgs ca) {
     for (int c = tid; c < kp; c += TPB) {
       for (int i = 0; i < kp; ++i) {
         double s = A1[c * KP + i];                 // (T^T)[i][c] = T[c][i]
+#pragma unroll 8
         for (int mm = 0; mm < i; ++mm) s -= A2[i * KP + mm] * A0[mm * KP + c];
         A0[i * KP + c] = s / A2[i * KP + i];
       }
@@ -1096,6 +1198,7 @@ __global__ void __launch_bounds__(TPB) k_coarse(CoarseArgs ca) {
     for (int e = tid; e < kp * kp; e += TPB) {
       const int aa = e / kp, bb = e % kp;
       double s = 0.0;
+#pragma unroll 8
       for (int i = 0; i < nx; ++i) s += A0[i * KP + aa] * A0[i * KP + bb];
       Cm[kidx[aa] * KP + kidx[bb]] = s;
     }

@@ -463,6 +463,20 @@ __global__ void k_fill(V* p, int64_t n, V val) {
   for (int64_t j = i; j < n; j += stride) p[j] = val;
 }
 
+// n zeros in each of a list of arrays, one launch for all
+template <typename V>
+struct FillList {
+  V* p[8];
+  int n;
+  void add(V* q) { if (q) p[n++] = q; }     // (arrays this configuration does without are null)
+};
+template <typename V>
+__global__ void k_fill_zero(FillList<V> l, int64_t n) {
+  V* p = l.p[blockIdx.y];
+  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x)
+    p[j] = (V)0;
+}
+
 // padded copy: dst[m*vs + i] = src[m*N + i]
 __global__ void k_copy_padded(int64_t N, const double* src, double* dst, int64_t vs) {
   const int m = blockIdx.y;
