@@ -222,6 +222,10 @@ struct adef2_ctx {
   // persistent chunk kernel (k_persist): rows per block, 0 = one kernel per
   // step; its exchange buffers, launches so far and arrivals they add up to
   int ps_rows = 0;
+  std::vector<int> live_h;       // instances of the persistent launches, and their
+  int* live_d = nullptr;         //   list on the device (live_cap entries)
+  size_t live_cap = 0;
+  int nlive = 0;
   int n_cu = 0;
   unsigned* ps_flags = nullptr;
   double *ps_pw = nullptr, *ps_dots = nullptr;
@@ -342,7 +346,7 @@ void free_all(adef2_ctx* c) {
   F(c->W64); F(c->W32); F(c->dinv64); F(c->dinv32); F(c->x64); F(c->r64); F(c->x0pad);
   F(c->t64); F(c->t32); F(c->Tm); F(c->dia1_64); F(c->dia1_32);
   F(c->part); F(c->ctr);
-  F(c->ps_flags); F(c->ps_pw); F(c->ps_dots); F(c->ps_shake);
+  F(c->ps_flags); F(c->ps_pw); F(c->ps_dots); F(c->ps_shake); F(c->live_d);
   F(c->pt_P); F(c->pt_T); F(c->pt_Q); F(c->pt_X); F(c->pt_D); F(c->pt_flags); F(c->pt_pw); F(c->pt_dots); F(c->pt_pub);
   F(c->Phi); F(c->mlp); F(c->mlp_bf); F(c->mlp_g); F(c->mlp_part); F(c->mlp_m); F(c->mlp_v); F(c->theta_tr);
   F(c->Htr); F(c->Ntr); F(c->gtr); F(c->e0tr); F(c->bxtr); F(c->act); F(c->mout); F(c->dout); F(c->dA1);
@@ -1038,7 +1042,7 @@ int persist_form(const adef2_ctx* c) {
   // against free: 11.2 / 13.1 us at 63^2, k = 16 (1 MB); 22.6 / 25.9 us at
   // 255^2, k = 40 (42 MB); 36.9 / 33.1 us at 127^2 x 16, k = 40 (88 MB);
   // 53.4 / 49.3 us at 100^2 x 30, k = 40 (99 MB)
-  const double panels = 8.0 * c->N * c->KP * (c->B + (c->zs ? c->B : 1));
+  const double panels = 8.0 * c->N * c->KP * (c->nlive + (c->zs ? c->nlive : 1));
   return panels > 64e6 ? PS_FREE : PS_STORED;
 }
 
@@ -1070,7 +1074,7 @@ int persist_rows(adef2_ctx* c) {
   if (c->ne > 0 && (c->zs != 0 || c->n_eig != c->k)) return 0;
   if (!device_cus(c)) return 0;
   for (int R : {256, 512, 1024}) {
-    const int64_t blocks = cdiv(c->N, (int64_t)R) * c->B;
+    const int64_t blocks = cdiv(c->N, (int64_t)R) * c->nlive;
     if ((R == 256 && blocks > 128) || (R == 512 && blocks > c->n_cu)) continue;
     const int form = persist_form(c);
     const void* fn = mat64(c->prec)   ? (const void*)persist_fn<double, double>(c->KP, R, form)
@@ -1099,7 +1103,8 @@ int persist_shake(adef2_ctx* c) {
 
 // exchange buffers for the current batch
 int persist_buffers(adef2_ctx* c) {
-  const size_t tiles = (size_t)cdiv(c->N, (int64_t)c->ps_rows) * c->B;
+  // (room for every plan with up to two blocks per compute unit)
+  const size_t tiles = std::max((size_t)cdiv(c->N, (int64_t)c->ps_rows) * c->nlive, 2 * (size_t)c->n_cu);
   const size_t vals = tiles * (2 * c->KP + 2);
   int rc;
   if ((rc = persist_shake(c))) return rc;
@@ -1124,7 +1129,9 @@ void launch_persist(adef2_ctx* c, const IterArgs<V, M>& a, int chunk, hipStream_
   pa.dots = c->ps_dots;
   pa.shake = c->ps_shake;
   pa.nt = (int)cdiv(c->N, (int64_t)c->ps_rows);
-  pa.nblk = (unsigned)(pa.nt * c->B);
+  pa.ids = c->live_d;
+  pa.nb = c->nlive;
+  pa.nblk = (unsigned)(pa.nt * c->nlive);
   pa.seq = ++c->ps_seq;
   pa.base = c->ps_base;
   c->ps_base += pa.nblk;
@@ -1166,7 +1173,7 @@ bool persist_tm_plan(adef2_ctx* c) {
   if ((og.D != 5 && og.D != 7) || og.d0 != og.D / 2 || (c->factored && (og.D1 != og.D || og.d01 != og.D / 2)))
     return false;
   if (!device_cus(c)) return false;
-  const int ng = (int)cdiv(c->B, PT_G);
+  const int ng = (int)cdiv(c->nlive, PT_G);
   const int most = c->n_cu / ng;
   if (most < 1) return false;
   c->pt_er = (int)cdiv(cdiv(c->N, (int64_t)most), (int64_t)PT_STEP);
@@ -1194,7 +1201,7 @@ bool persist_tm_plan(adef2_ctx* c) {
 }
 
 int persist_tm_buffers(adef2_ctx* c) {
-  const int ng = (int)cdiv(c->B, PT_G);
+  const int ng = (int)cdiv(c->nlive, PT_G);
   const size_t row = (size_t)(c->N + 2 * c->H) * PT_G, n = row * ng;
   int rc;
   if (c->pt_N != c->N || c->pt_H != c->H || c->pt_ng < ng) {
@@ -1219,7 +1226,7 @@ int persist_tm_buffers(adef2_ctx* c) {
   }
   if (c->pt_e > 8 && !c->pt_X && (rc = dalloc(c, &c->pt_X, na))) return rc;
   if (c->pt_e > 16 && !c->pt_D && (rc = dalloc(c, &c->pt_D, na))) return rc;
-  const size_t tiles = (size_t)ng * c->pt_nt, vals = (size_t)c->B * c->pt_nt * (2 * c->KP + 2),
+  const size_t tiles = std::max((size_t)ng * c->pt_nt, (size_t)c->n_cu), vals = tiles * PT_G * (2 * c->KP + 2),
                pubs = (size_t)ng * PT_G * (c->KP + 3);
   if (tiles > c->pt_tiles) {
     c->pt_tiles = 0;
@@ -1254,7 +1261,9 @@ void launch_persist_tm(adef2_ctx* c, const IterArgs<double, float>& a, int chunk
   pa.gs = (c->N + 2 * c->H) * PT_G;
   pa.shake = c->ps_shake;
   pa.nt = c->pt_nt;
-  pa.ng = (int)cdiv(c->B, PT_G);
+  pa.ng = (int)cdiv(c->nlive, PT_G);
+  pa.ids = c->live_d;
+  pa.nb = c->nlive;
   pa.nblk = (unsigned)(pa.nt * pa.ng);
   pa.seq = ++c->ps_seq;
   pa.base = c->ps_base;
@@ -1267,6 +1276,37 @@ void launch_persist_tm(adef2_ctx* c, const IterArgs<double, float>& a, int chunk
   pa.fused = c->pt_fused;
   hipLaunchKernelGGL((persist_tm_fn(c->KP, c->pt_e)), dim3((unsigned)(8 * cdiv(pa.nblk, 8))), dim3(PT_TB),
                      persist_tm_lds(c), s, a, pa);
+}
+
+// Persistent kernel for the nlive instances that still iterate, if one applies
+bool persist_plan(adef2_ctx* c) {
+  c->pt_e = 0;
+  c->ps_rows = persist_rows(c);
+  return c->ps_rows > 0 || persist_tm_plan(c);
+}
+
+// Takes the instances that still iterate (all: every one) as the list of the
+// persistent kernels' next launches and plans for them; persist: whether one
+// applies.  The stream is idle when the list changes.
+int persist_live(adef2_ctx* c, bool all, bool outer, bool* persist) {
+  std::vector<int> ids;
+  for (int m = 0; m < c->B; ++m) {
+    const Inst& s = c->inst_h[m];
+    if (all || !(outer ? s.outer_done : (s.done || s.outer_done))) ids.push_back(m);
+  }
+  if (!all && ids == c->live_h) return ADEF2_OK;
+  c->live_h = ids;
+  c->nlive = (int)ids.size();
+  *persist = c->nlive > 0 && persist_plan(c);
+  if (!*persist) return ADEF2_OK;
+  int rc;
+  if ((size_t)c->B > c->live_cap) {
+    c->live_cap = 0;
+    if ((rc = dalloc(c, &c->live_d, (size_t)c->B))) return rc;
+    c->live_cap = c->B;
+  }
+  HIPCHK(c, hipMemcpyAsync(c->live_d, c->live_h.data(), sizeof(int) * c->nlive, hipMemcpyHostToDevice, c->st));
+  return c->pt_e ? persist_tm_buffers(c) : persist_buffers(c);
 }
 
 // max_chunks > 0 stops after that many chunks (tuning trials).
@@ -1341,9 +1381,9 @@ int run_sweep(adef2_ctx* c, const double* src, const double* x0pad, double thres
   const int chunk = std::max(1, c->o.check_every);
   // one chunk of iterations on stream s (kernel arguments are the same for
   // every iteration: all per-iteration state lives in device memory)
-  bool persist = c->ps_rows > 0 || c->pt_e > 0;
-  if (persist) {
-    int rc = c->pt_e ? persist_tm_buffers(c) : persist_buffers(c);
+  bool persist = false, may_persist = max_chunks == 0;
+  if (may_persist) {
+    int rc = persist_live(c, true, b_outer != nullptr, &persist);
     if (rc) return rc;
   }
   auto launch_chunk = [&](hipStream_t s) {
@@ -1459,12 +1499,12 @@ int run_sweep(adef2_ctx* c, const double* src, const double* x0pad, double thres
       int off = 0;
       for (int m = 0; m < c->B; ++m) off = std::max(off, (int)c->inst_h[m].off);
       if (off == 2) return fail(c, ADEF2_E_HIP, "persistent iteration kernel: a block did not answer");
-      if (off == 1) {
-        persist = false;
-        if ((grc = make_graph())) return grc;
-      }
+      if (off == 1) persist = may_persist = false;
     }
     if (ad) break;
+    // fewer instances may fit where all did not, or need fewer tiles or groups
+    if (may_persist && (rc = persist_live(c, false, b_outer != nullptr, &persist))) return rc;
+    if (!persist && !gexec && (grc = make_graph())) return grc;
     // every instance stops at maxit on the device; this guards the host loop
     if (launched > (int64_t)c->o.maxit + (int64_t)(pmax + 2) * chunk)
       return fail(c, ADEF2_E_HIP, "iteration kernels made no progress");
@@ -1490,7 +1530,7 @@ int run_sweep(adef2_ctx* c, const double* src, const double* x0pad, double thres
     for (int rep = 0; rep < nrep; ++rep) {
       launched += chunk;
       if (c->o.profile) bm = byte_model(c, (double)sizeof(V), (double)sizeof(M), true);
-      if (gexec) {
+      if (gexec && !persist) {
         HIPCHK(c, hipEventRecord(c->gev_in, c->st));
         HIPCHK(c, hipStreamWaitEvent(c->gst, c->gev_in, 0));
         HIPCHK(c, hipGraphLaunch(gexec, c->gst));
@@ -1548,16 +1588,10 @@ int choose_variant(adef2_ctx* c, const double* b) {
                 "the tile-major boundary-form update needs FP32 panels with FP64 vectors (MIXED_REFINE), "
                 "reference modes shared by all instances that are eigenvectors of the reference operator, "
                 "and w_boundary enabled");
-  if (const int R = persist_rows(c)) {
+  c->nlive = c->B;
+  if (persist_plan(c)) {
     // (the variant of the kernel-per-step form, in case a chunk is called off)
     set_variant(c, 2, c->tm_ok ? 3 : persist_form(c) == PS_FREE ? 2 : 0, opf_default_rows(c));
-    c->ps_rows = R;
-    return ADEF2_OK;
-  }
-  if (persist_tm_plan(c)) {
-    const int E = c->pt_e;
-    set_variant(c, 2, 3, opf_default_rows(c));
-    c->pt_e = E;
     return ADEF2_OK;
   }
   // fused operator pass: the (tile height, instances per block) candidates

@@ -43,14 +43,16 @@ constexpr unsigned long long PS_EMPTY = 0x7FF4A5A55A5A4321ull;   // signalling N
 enum { PS_ARRIVED = 0, PS_DECISION = 16, PS_LOST = 32, PS_WORDS = 48 };
 
 struct PersistArgs {
-  unsigned* flags;      // [B][nt] step counters
-  double* pw;           // [3][B][nt] partial sums of p.w
-  double* dots;         // [3][B][nt][2 KP + 2] partial sums of the update
+  unsigned* flags;      // [nb][nt] step counters
+  double* pw;           // [3][nb][nt] partial sums of p.w
+  double* dots;         // [3][nb][nt][2 KP + 2] partial sums of the update
   unsigned* shake;      // PS_WORDS words: arrivals, decision, lost waits
   unsigned seq;         // number of this launch (from 1)
   unsigned base;        // arrivals before this launch
   unsigned nblk;        // blocks that arrive
   int nt;               // tiles of an instance
+  const int* ids;       // the instances of this launch (those still iterating), nb of them
+  int nb;
   int chunk;            // iterations
   int reach1, reach;    // reach of the inner (factored) and of the outer stencil
   int fused;            // the inner product stays in LDS, its halo formed twice
@@ -378,15 +380,16 @@ k_persist(IterArgs<V, M> a, PersistArgs pa) {
   __shared__ double s_tot[2];                // r.y, r.r
   __shared__ short blist[SPEC ? R : 1];
   __shared__ int bcnt[SPEC ? R / 64 + 1 : 1];
-  int tile, m;
-  ps_place(a.B, tile, m);
+  int tile, place;
+  ps_place(pa.nb, tile, place);
   if (tile >= pa.nt) return;
   const int t0_ = threadIdx.x, wid = __builtin_amdgcn_readfirstlane(t0_ >> 6);
+  const int m = pa.ids[place];
   Inst* S = a.inst + m;
   const bool idle = S->done;
-  unsigned* flag = pa.flags + (size_t)m * pa.nt;
+  unsigned* flag = pa.flags + (size_t)place * pa.nt;
   unsigned* lost = pa.shake + PS_LOST;
-  const size_t team = (size_t)m * pa.nt, all = (size_t)a.B * pa.nt;
+  const size_t team = (size_t)place * pa.nt, all = (size_t)pa.nb * pa.nt;
   double rho = S->rho, beta = S->fresh ? 0.0 : S->beta;
   double rr_last = S->rr, pw_last = S->pw, rho_end = S->rho_end;
   const double thresh2 = S->thresh2, sa = S->a, sc = S->c;

@@ -39,7 +39,7 @@ constexpr int PT_STEP = 4 * PT_NW;        // rows of a block per step
 struct PersistTmArgs {
   unsigned* flags;      // [groups][nt] step counters
   double* pw;           // [3][groups][nt][16]
-  double* dots;         // [3][B][nt][2 KP + 2]
+  double* dots;         // [3][nb][nt][2 KP + 2]
   double* pub;          // [3][groups][16][KP + 3]: coordinates, beta, r.y, go on (0) or not
   double* P;            // rows of 16 instances, [groups][N + 2 halo][16]: p,
   double* T;            //   A p (while it goes through memory),
@@ -50,6 +50,8 @@ struct PersistTmArgs {
   unsigned* shake;
   unsigned seq, base, nblk;
   int nt, ng;           // tiles, groups
+  const int* ids;       // the instances of this launch (those still iterating), nb of them
+  int nb;
   int rows, er;         // rows per tile (PT_STEP er) and steps
   int chunk;
   int reach1, reach, fused;
@@ -143,10 +145,11 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
   const int t0_ = threadIdx.x;
   const int wid = __builtin_amdgcn_readfirstlane(t0_ >> 6);
   const int g0 = grp * PT_G;
-  const int G = min(PT_G, a.B - g0);
+  const int G = min(PT_G, pa.nb - g0);
+  const int* ids = pa.ids + g0;              // the group's instances
   unsigned* flag = pa.flags + (size_t)grp * pa.nt;
   unsigned* lost = pa.shake + PS_LOST;
-  const size_t allpw = (size_t)pa.ng * pa.nt * PT_G, alld = (size_t)a.B * pa.nt * NV, allp = (size_t)pa.ng * PT_G * NP;
+  const size_t allpw = (size_t)pa.ng * pa.nt * PT_G, alld = (size_t)pa.nb * pa.nt * NV, allp = (size_t)pa.ng * PT_G * NP;
   // the instances this block leads, spread over the tiles
   unsigned lead = 0u;
   for (int i = 0; i < G; ++i)
@@ -159,7 +162,7 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
     s_done[i] = 0;
     e0s[i] = e1s[i] = 0;
     if (i < G) {
-      const Inst* S = a.inst + g0 + i;
+      const Inst* S = a.inst + ids[i];
       s_live[i] = !S->done;
       s_fresh[i] = S->fresh;
       s_defl[i] = S->kk > 0;
@@ -172,10 +175,10 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
   }
   if (t0_ == 0) s_bad = 0;
   if (KP <= 40 && lead)
-    for (int e = t0_; e < KP * KP; e += PT_TB) Cl[e] = a.C[(size_t)(g0 + __ffs(lead) - 1) * KP * KP + e];
+    for (int e = t0_; e < KP * KP; e += PT_TB) Cl[e] = a.C[(size_t)ids[__ffs(lead) - 1] * KP * KP + e];
   for (int e = t0_; e < PT_G * KP; e += PT_TB) {
     const int i = e / KP, q = e - i * KP;
-    cfs[i][q] = i < G ? a.inst[g0 + i].coef[q] : 0.0;
+    cfs[i][q] = i < G ? a.inst[ids[i]].coef[q] : 0.0;
   }
   // own counters and slots empty before any block is let go
   if (t0_ == 0) st_agent(flag + tile, 0u);
@@ -193,7 +196,7 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
   };
   for (int sl = 0; sl < 3; ++sl) clear(t0_, sl);
   if (!ps_handshake(pt_shake_args(pa))) {
-    if (tile == 0 && t0_ < G) a.inst[g0 + t0_].off = 1;
+    if (tile == 0 && t0_ < G) a.inst[ids[t0_]].off = 1;
     return;
   }
   const int64_t N = a.op.N;
@@ -210,8 +213,9 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
   unsigned on = 0u, bnd = 0u;                // bit s: row inactive and inside; a listed row
   {
     const int i = t0_ & 15, j0 = wid * 4 * er + ((t0_ >> 4) & 3);
-    const int64_t vi = (int64_t)(g0 + i) * a.vs;
-    const size_t mi = (size_t)(g0 + i) * N;
+    const int id = ids[i < G ? i : 0];
+    const int64_t vi = (int64_t)id * a.vs;
+    const size_t mi = (size_t)id * N;
 #pragma unroll
     for (int s = 0; s < E; ++s) {
       r[s] = 0.0;
@@ -245,7 +249,7 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
     // row order
     if (t0_ < 2 * PT_G && (t0_ >> 1) < G) {
       const int i = t0_ >> 1;
-      const int32_t* to = a.btoff + (size_t)(g0 + i) * (a.ub_ntiles + 1);
+      const int32_t* to = a.btoff + (size_t)ids[i] * (a.ub_ntiles + 1);
       int lo = to[0], hi = to[a.ub_ntiles];
       const int64_t row = (t0_ & 1) ? base + rows : base;
       while (lo < hi) {
@@ -778,7 +782,7 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
               }
             };
             if (KP <= 40 && !(lead & (lead - 1u))) solve(Cl);
-            else solve(a.C + (size_t)(g0 + li) * KP * KP);
+            else solve(a.C + (size_t)ids[li] * KP * KP);
             cq += c1;
           }
           corr = ps_wave_sum(lane < KP ? tr * cq : 0.0);
@@ -830,14 +834,15 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
   }
   {
     const int i = t0_ & 15, j0 = wid * 4 * er + ((t0_ >> 4) & 3);
-    const int64_t vi = (int64_t)(g0 + i) * a.vs;
+    const int id = ids[i < G ? i : 0];
+    const int64_t vi = (int64_t)id * a.vs;
 #pragma unroll
     for (int s = 0; s < E; ++s)
       if ((on >> s) & 1u) {
         const int64_t gi = base + j0 + 4 * s;
         double xs, zs;
         if constexpr (KEEPX) xs = x[s]; else xs = Xg[gi * PT_G + i];
-        if constexpr (KEEPD) zs = dv[s] * r[s]; else zs = a.dinv[(size_t)(g0 + i) * N + gi] * r[s];
+        if constexpr (KEEPD) zs = dv[s] * r[s]; else zs = a.dinv[(size_t)id * N + gi] * r[s];
         a.x[vi + gi] = xs;
         a.r[vi + gi] = r[s];
         a.z[vi + gi] = zs;
@@ -847,7 +852,7 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
   __syncthreads();
   for (int i = 0; i < G; ++i) {
     if (!leads(i) || !s_was[i]) continue;      // s_was is 0 for instances idle from the start
-    Inst* S = a.inst + g0 + i;
+    Inst* S = a.inst + ids[i];
     for (int q = t0_; q < KP; q += PT_TB) S->coef[q] = cfs[i][q];
     if (t0_ == 0) {
       S->rho = s_rho[i]; S->beta = s_beta[i]; S->alpha = s_alpha[i]; S->rr = s_rr[i]; S->pw = s_pw[i];

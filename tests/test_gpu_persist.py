@@ -147,3 +147,33 @@ def test_group_chunk_kernel_matches_oracle(lib, kind, n, k, B):
         assert out["status"][m] == 0 and out["relres_true"][m] <= tol
         assert np.all(X[m, masks[m] == 1] == 0.0)
         assert e <= max(1e-8, 2 * e0), (m, e)
+
+
+@pytest.mark.parametrize("prec,n,B", [("fp64", 95, 60), ("fp32", 95, 60), ("mixed", 191, 40)])
+def test_instances_left_go_on_in_smaller_launches(lib, prec, n, B):
+    """Iteration counts that differ by more than two: a batch too large for the
+    chunk kernel starts with a kernel per step (groups of 16 in mixed precision)
+    and its last instances go on in chunk launches of their own."""
+    w = gen.c3_workload(n=n, k=16, B=B)
+    masks = np.stack([i.mask for i in w.instances])
+    bs = np.stack([i.b for i in w.instances])
+    case(f"instances left {prec} het n={n} B={B}")
+    s = solver(lib, w.op, w.Z, "factored", profile=1,
+               precision=dict(fp64=lib.FP64, mixed=lib.MIXED_REFINE, fp32=lib.FP32_REFINE)[prec])
+    scale = np.array([i.a for i in w.instances])
+    out = s.solve_batched(masks, bs, 1e-8, a=scale)
+    st = s.stats()
+    assert out["iters"].max() > 2 * out["iters"].min()
+    assert st["chunk"]["launches"] > 0
+    if prec != "mixed":
+        assert st["pupdate"]["launches"] + st["pupdate_bt"]["launches"] > 0
+    X = out["x"].cpu().numpy()
+    order = np.argsort(out["iters"])
+    for m in (order[0], order[B // 2], order[-1]):
+        S = spec(w.op, "factored", a=scale[m], c=scale[m] * w.op.shift)
+        I, xs = _xstar(S, masks[m], bs[m])
+        ref = oracle.solve_instance(S, w.Z, masks[m], bs[m], 1e-8)
+        e, e0 = oracle.rel_err(X[m, I], xs), oracle.rel_err(ref.x[I], xs)
+        print(f"   m={m} iters {out['iters'][m]} (oracle {ref.iters}) e_rel {e:.2e} (oracle {e0:.2e})", flush=True)
+        assert out["status"][m] == 0
+        assert e <= max(1e-8, 2 * e0), (m, e)
