@@ -131,12 +131,14 @@ typedef struct {
                            residual exceeds the segment's final recurrence
                            residual by more than 2x (drift), when the next
                            segment restarts; 0                              */
-  int32_t check_every;  /* iterations per chunk: one launch of the persistent
-                           chunk kernel where it applies (rows_per_thread,
+  int32_t check_every;  /* iterations per chunk: one launch of a persistent
+                           chunk kernel where one applies (rows_per_thread,
                            w_mode, op_fused, op_rows, op_group and update_ws
-                           all 0 and a batch whose blocks are all resident at
-                           once), else one HIP graph of check_every iterations
-                           of every kernel; 32                              */
+                           all 0, and the blocks of the instances that still
+                           iterate all resident at once: per instance, or in
+                           groups of 16 in the boundary form), else one HIP
+                           graph of check_every iterations of every kernel;
+                           32                                               */
   int32_t rows_per_thread; /* rows per thread of the per-instance iteration
                            kernels (tile height 256 or 512 rows): 1 or 2, or
                            0 = tuned on the first solve of each
@@ -184,7 +186,7 @@ typedef struct {
                            as 1 when every shared reference mode passes the
                            test, else 0.  0: W stored and read whole      */
   int32_t graph;        /* 1 (default): each chunk of check_every iterations
-                           is captured once into a HIP graph (per kernel
+                           that runs as a kernel per step is captured once into a HIP graph (per kernel
                            arguments) and replayed on a private stream of the
                            context, ordered against its stream by events;
                            0: kernels launched one by one.  profile = 1

@@ -22,7 +22,7 @@
 // ten loads of 128 bytes, and 26 of the 45 us of an iteration at 255^2 x 16 go
 // there and into the four exchanges), not HBM.  An iteration, against a kernel
 // per step: 255^2 x 16, k = 32: 70.0 -> 44.7 us; 383^2 x 16: 109 -> 77;
-// 191^2 x 48 (13-point S): 73.9 -> 59.7; 127^2 x 40: 72.3 -> 41.5.
+// 191^2 x 48: 73.9 -> 59.7; 127^2 x 40: 72.3 -> 41.5.
 #pragma once
 #include <type_traits>
 
