@@ -679,7 +679,8 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
 #pragma unroll
                 for (int u = 0; u < 16; ++u) {
                   const int q = k + u * (64 / KL);
-                  ab += (double)bw[u] * zb[q < k1 ? q : 0];
+                  // (past the end: slot 0 is another instance's, which may hold Inf)
+                  ab += (double)bw[u] * (q < k1 ? zb[q] : 0.0);
                 }
               }
             } else {

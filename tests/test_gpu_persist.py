@@ -177,3 +177,34 @@ def test_instances_left_go_on_in_smaller_launches(lib, prec, n, B):
         print(f"   m={m} iters {out['iters'][m]} (oracle {ref.iters}) e_rel {e:.2e} (oracle {e0:.2e})", flush=True)
         assert out["status"][m] == 0
         assert e <= max(1e-8, 2 * e0), (m, e)
+
+
+def test_breakdown_stays_in_its_instance(lib):
+    """Instance 0 of a group overflows in its first iteration: its operator is
+    1e-315 times the others' and shifted below a Ritz value of the modes (so that it
+    runs without them), alpha = r.r / p.S p is infinite, and so is its z on its
+    listed rows, the first of every tile's list. The other instances get the
+    solutions they get beside a sound instance 0."""
+    n, k, B, tol = 91, 8, 57, 1e-8
+    op, Z, masks, bs = _problem("cd", n, k, B)
+    bs[0] = np.random.default_rng(3).standard_normal(op.N)
+    case(f"breakdown in a group, mixed cd n={n} k={k} B={B}")
+    out = []
+    for broken in (False, True):
+        s = solver(lib, op, Z, "factored", profile=1, precision=lib.MIXED_REFINE, precond=lib.NONE)
+        s._check = lambda rc, **kw: rc
+        a, c = np.ones(B), np.zeros(B)
+        if broken:
+            a[0], c[0] = 1e-315, -1.9e-310
+        out.append(s.solve_batched(masks, bs, tol, a=a, c=c))
+        st = s.stats()
+        assert st["chunk"]["launches"] > 0 and st["update_tm"]["launches"] == 0
+    sound, broken = out
+    assert broken["status"][0] < 0
+    assert np.all(sound["status"] == 0)
+    assert np.all(broken["status"][1:] == 0), broken["status"]
+    assert np.all(broken["relres_true"][1:] <= tol)
+    x0, x1 = sound["x"].cpu().numpy(), broken["x"].cpu().numpy()
+    for m in range(1, B):
+        # both solve to a relative residual of tol, cond(S) <= 3e5
+        assert np.linalg.norm(x1[m] - x0[m]) <= 2 * 3e5 * tol * np.linalg.norm(x0[m]), m
