@@ -578,6 +578,24 @@ int adef2_operator_variant(adef2_ctx *ctx, int32_t *fused, int32_t *tile_rows, i
  * E_STATE before the first solve. */
 int adef2_update_variant(adef2_ctx *ctx, int32_t *warp_specialised, int32_t *tiles_per_block, float *ms);
 
+/* Chunk launches (persistent kernels, see opts.check_every) of the last solve on
+ * ctx: form of the first one (0: none, the solve ran a kernel per step; 1: one
+ * instance per block; 2: groups of 16 instances), its rows per block and the
+ * number of launches.  lost: solves of this context that a block gave up in (see
+ * adef2_set_chunk_bounds).  Any pointer may be NULL.  E_STATE before the first
+ * solve. */
+int adef2_chunk_variant(adef2_ctx *ctx, int32_t *form, int32_t *rows, int64_t *launches, int64_t *lost);
+
+/* Bounds of the chunk launches' waits, for a GPU that is shared with other work;
+ * < 0: the default.  handshake_us (20 ms): a launch whose blocks have not all
+ * started within it is called off before it changes anything, and the solve goes
+ * on with a kernel per step; 0: every launch is called off.  wait_us (4 s): a
+ * block that waits longer for another one gives the launch up, and the solve
+ * starts again with a kernel per step; 0: the first wait that is not over at once.
+ * from_launch: the chunk launch of a solve (from 0) from which on the two hold;
+ * before it the defaults do.  At most 1e9 us each (E_ARG). */
+int adef2_set_chunk_bounds(adef2_ctx *ctx, int64_t handshake_us, int64_t wait_us, int32_t from_launch);
+
 #define ADEF2_STATS_KERNELS 24
 typedef struct {
   int32_t n_kernels;            /* entries filled                           */

@@ -57,6 +57,12 @@ constexpr double FP32_DROP = 1e-3;   // column-drop threshold with FP32 panels
 // the order of the FP32 rounding (6e-8) of the stored W that the mixed
 // iteration carries anyway; the FP64 residual replacement keeps the accuracy
 constexpr double EIG_TOL = 1e-6;
+// Bounds of the persistent chunk kernels: blocks of a launch that fits an idle GPU
+// start within microseconds, so 20 ms means that other work holds compute units;
+// a wait is an iteration of another block (10-200 us), 4 s allow for a GPU that is
+// shared in time slices.
+constexpr int64_t PS_SHAKE_US = 20000, PS_WAIT_US = 4000000;
+constexpr int RC_REDO = -1000;                 // (internal) solve again without chunk launches
 constexpr double FP32_COND = 1e-3 / 5.96e-8;   // learned cond(E) bound with FP32 panels
 
 enum KernelId { KI_INIT = 0, KI_INIT2, KI_PUPDATE, KI_SPMV, KI_UPDATE, KI_RESID, KI_ACCUM,
@@ -232,6 +238,15 @@ struct adef2_ctx {
   unsigned* ps_shake = nullptr;
   size_t ps_tiles = 0, ps_vals = 0;   // tiles, and tiles times values, allocated
   unsigned ps_seq = 0, ps_base = 0;
+  bool ps_ready = false;         // handshake words cleared for this sequence of launches
+  // bounds of the handshake and of a wait in us, kept from launch ps_from of a
+  // solve on (before it the defaults are)
+  int64_t ps_shake_us = PS_SHAKE_US, ps_wait_us = PS_WAIT_US;
+  int ps_from = 0;
+  bool no_chunk = false;         // this solve runs without chunk launches
+  // the last solve's chunk launches: how many, and the first one's form and rows
+  int64_t ch_launches = 0, ch_lost = 0;
+  int ch_form = 0, ch_rows = 0;
   // persistent tile-major chunk kernel (k_persist_tm): steps its registers are
   // laid out for (0: not in use), steps and rows per tile; rows of 16 instances
   int pt_e = 0, pt_er = 0, pt_rows = 0, pt_nt = 0;
@@ -1091,14 +1106,34 @@ int persist_rows(adef2_ctx* c) {
   return 0;
 }
 
-// words of the handshake
+// words of the handshake, cleared once per sequence of launches (a launch that
+// was halted in an earlier one leaves the halt word set)
 int persist_shake(adef2_ctx* c) {
-  if (c->ps_shake) return ADEF2_OK;
   int rc;
-  if ((rc = dalloc(c, &c->ps_shake, PS_WORDS))) return rc;
-  fill<unsigned>(c, c->ps_shake, PS_WORDS, 0u);
-  c->ps_seq = c->ps_base = 0;
+  if (!c->ps_shake && (rc = dalloc(c, &c->ps_shake, PS_WORDS))) return rc;
+  if (!c->ps_ready) {
+    fill<unsigned>(c, c->ps_shake, PS_WORDS, 0u);
+    c->ps_seq = c->ps_base = 0;
+    c->ps_ready = true;
+  }
   return ADEF2_OK;
+}
+
+// Bounds and number of the next launch of nblk blocks
+template <typename Args>
+void persist_launch_args(adef2_ctx* c, Args& pa) {
+  const bool own = c->ch_launches >= c->ps_from;
+  const int64_t sh = own ? c->ps_shake_us : PS_SHAKE_US, wt = own ? c->ps_wait_us : PS_WAIT_US;
+  pa.shake = c->ps_shake;
+  pa.shake_ticks = sh > 0 ? sh * PS_TICKS_US : -1;
+  pa.wait_ticks = wt > 0 ? wt * PS_TICKS_US : -1;
+  pa.seq = ++c->ps_seq;
+  pa.base = c->ps_base;
+  c->ps_base += pa.nblk;
+  if (c->ch_launches++ == 0) {
+    c->ch_form = c->pt_e ? 2 : 1;
+    c->ch_rows = c->pt_e ? c->pt_rows : c->ps_rows;
+  }
 }
 
 // exchange buffers for the current batch
@@ -1127,14 +1162,11 @@ void launch_persist(adef2_ctx* c, const IterArgs<V, M>& a, int chunk, hipStream_
   pa.flags = c->ps_flags;
   pa.pw = c->ps_pw;
   pa.dots = c->ps_dots;
-  pa.shake = c->ps_shake;
   pa.nt = (int)cdiv(c->N, (int64_t)c->ps_rows);
   pa.ids = c->live_d;
   pa.nb = c->nlive;
   pa.nblk = (unsigned)(pa.nt * c->nlive);
-  pa.seq = ++c->ps_seq;
-  pa.base = c->ps_base;
-  c->ps_base += pa.nblk;
+  persist_launch_args(c, pa);
   pa.chunk = chunk;
   pa.reach = op_reach(c->offs);
   pa.reach1 = c->factored ? op_reach(c->offs1) : 0;
@@ -1259,15 +1291,12 @@ void launch_persist_tm(adef2_ctx* c, const IterArgs<double, float>& a, int chunk
   pa.X = c->pt_X ? c->pt_X + halo : nullptr;
   pa.D = c->pt_D ? c->pt_D + halo : nullptr;
   pa.gs = (c->N + 2 * c->H) * PT_G;
-  pa.shake = c->ps_shake;
   pa.nt = c->pt_nt;
   pa.ng = (int)cdiv(c->nlive, PT_G);
   pa.ids = c->live_d;
   pa.nb = c->nlive;
   pa.nblk = (unsigned)(pa.nt * pa.ng);
-  pa.seq = ++c->ps_seq;
-  pa.base = c->ps_base;
-  c->ps_base += pa.nblk;
+  persist_launch_args(c, pa);
   pa.rows = c->pt_rows;
   pa.er = c->pt_er;
   pa.chunk = chunk;
@@ -1381,7 +1410,8 @@ int run_sweep(adef2_ctx* c, const double* src, const double* x0pad, double thres
   const int chunk = std::max(1, c->o.check_every);
   // one chunk of iterations on stream s (kernel arguments are the same for
   // every iteration: all per-iteration state lives in device memory)
-  bool persist = false, may_persist = max_chunks == 0;
+  bool persist = false, may_persist = max_chunks == 0 && !c->no_chunk;
+  c->ps_ready = false;
   if (may_persist) {
     int rc = persist_live(c, true, b_outer != nullptr, &persist);
     if (rc) return rc;
@@ -1495,11 +1525,16 @@ int run_sweep(adef2_ctx* c, const double* src, const double* x0pad, double thres
     if (rc) return rc;
     if (persist) {
       // a chunk that was called off (not every block got a compute unit in
-      // time) has changed nothing: go on with one kernel per step
+      // time) has changed nothing: go on with one kernel per step.  A block that
+      // gave up a wait leaves the instance's vectors of different iterations:
+      // start again
       int off = 0;
       for (int m = 0; m < c->B; ++m) off = std::max(off, (int)c->inst_h[m].off);
-      if (off == 2) return fail(c, ADEF2_E_HIP, "persistent iteration kernel: a block did not answer");
-      if (off == 1) persist = may_persist = false;
+      if (off == PS_LOST) {
+        ++c->ch_lost;
+        return RC_REDO;
+      }
+      if (off == PS_OFF) persist = may_persist = false;
     }
     if (ad) break;
     // fewer instances may fit where all did not, or need fewer tiles or groups
@@ -1589,7 +1624,7 @@ int choose_variant(adef2_ctx* c, const double* b) {
                 "reference modes shared by all instances that are eigenvectors of the reference operator, "
                 "and w_boundary enabled");
   c->nlive = c->B;
-  if (persist_plan(c)) {
+  if (!c->no_chunk && persist_plan(c)) {
     // (the variant of the kernel-per-step form, in case a chunk is called off)
     set_variant(c, 2, c->tm_ok ? 3 : persist_form(c) == PS_FREE ? 2 : 0, opf_default_rows(c));
     return ADEF2_OK;
@@ -1728,10 +1763,8 @@ int choose_variant(adef2_ctx* c, const double* b) {
   return ADEF2_OK;
 }
 
-// Solve all B restricted instances; b, x instance-major unpadded [B][N].
-// tols: host f64[B] per-instance tolerances, or null for tol everywhere
-int solve_batch(adef2_ctx* c, const double* b, const double* x0, double tol, double* x,
-                const double* tols = nullptr) {
+// One attempt at solve_batch: RC_REDO when a chunk launch gave up a wait
+int solve_once(adef2_ctx* c, const double* b, const double* x0, double tol, double* x, const double* tols) {
   const int B = c->B;
   const int64_t N = c->N;
   c->tol_h.assign(B, tol);
@@ -1814,6 +1847,24 @@ int solve_batch(adef2_ctx* c, const double* b, const double* x0, double tol, dou
   if (c->o.profile) ev_harvest(c);
   c->solved = true;
   return ADEF2_OK;
+}
+
+// Solve all B restricted instances; b, x instance-major unpadded [B][N].
+// tols: host f64[B] per-instance tolerances, or null for tol everywhere.
+// (x is written last, so a second attempt starts from the same inputs.)
+int solve_batch(adef2_ctx* c, const double* b, const double* x0, double tol, double* x,
+                const double* tols = nullptr) {
+  c->no_chunk = false;
+  c->ch_launches = 0;
+  c->ch_form = c->ch_rows = 0;
+  int rc = solve_once(c, b, x0, tol, x, tols);
+  if (rc == RC_REDO) {
+    c->no_chunk = true;
+    c->ch_launches = 0;
+    c->ch_form = c->ch_rows = 0;
+    rc = solve_once(c, b, x0, tol, x, tols);
+  }
+  return rc;
 }
 
 int combine_status(const Inst& s) {
@@ -2632,6 +2683,26 @@ int adef2_variant(adef2_ctx* c, int32_t* rows_per_thread, int32_t* w_mode, float
       if (t.B == c->B && t.prec == c->prec && t.KP == c->KP && t.fact == fact && t.N == c->N)
         for (int i = 0; i < 10; ++i) ms[i] = t.ms[i];
   }
+  return ADEF2_OK;
+}
+
+int adef2_set_chunk_bounds(adef2_ctx* c, int64_t handshake_us, int64_t wait_us, int32_t from_launch) {
+  if (!c) return ADEF2_E_ARG;
+  if (handshake_us > 1000000000 || wait_us > 1000000000 || from_launch < 0)
+    return fail(c, ADEF2_E_ARG, "chunk bounds are at most 1e9 us, from_launch at least 0");
+  c->ps_shake_us = handshake_us < 0 ? PS_SHAKE_US : handshake_us;
+  c->ps_wait_us = wait_us < 0 ? PS_WAIT_US : wait_us;
+  c->ps_from = from_launch;
+  return ADEF2_OK;
+}
+
+int adef2_chunk_variant(adef2_ctx* c, int32_t* form, int32_t* rows, int64_t* launches, int64_t* lost) {
+  if (!c) return ADEF2_E_ARG;
+  if (!c->solved) return fail(c, ADEF2_E_STATE, "chunk_variant before the first solve");
+  if (form) *form = c->ch_form;
+  if (rows) *rows = c->ch_rows;
+  if (launches) *launches = c->ch_launches;
+  if (lost) *lost = c->ch_lost;
   return ADEF2_OK;
 }
 

@@ -49,6 +49,7 @@ struct PersistTmArgs {
   int64_t gs;           // stride of a group in P, T, Q, X, D
   unsigned* shake;
   unsigned seq, base, nblk;
+  long long shake_ticks, wait_ticks;
   int nt, ng;           // tiles, groups
   const int* ids;       // the instances of this launch (those still iterating), nb of them
   int nb;
@@ -61,18 +62,18 @@ struct PersistTmArgs {
 __device__ __forceinline__ PersistArgs pt_shake_args(const PersistTmArgs& a) {
   PersistArgs p{};
   p.shake = a.shake; p.seq = a.seq; p.base = a.base; p.nblk = a.nblk;
+  p.shake_ticks = a.shake_ticks;
   return p;
 }
 
 // Value at p once it has arrived (bounded; ok becomes false past the bound).
-__device__ __forceinline__ double pt_take(const double* p, unsigned* lost, bool& ok) {
+__device__ __forceinline__ double pt_take(const double* p, const PsBound& bound, bool& ok) {
   unsigned long long b = ps_bits(p);
   if (b == PS_EMPTY) {
     const long long c0 = wall_clock64();
     int n = 0;
     while ((b = ps_bits(p)) == PS_EMPTY) {
-      if ((++n & 63) == 0 && (ld_agent(lost) != 0u || wall_clock64() - c0 > PS_WAIT_TICKS)) {
-        st_agent(lost, 1u);
+      if ((++n & 63) == 0 && bound.lost(c0)) {
         ok = false;
         break;
       }
@@ -148,7 +149,7 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
   const int G = min(PT_G, pa.nb - g0);
   const int* ids = pa.ids + g0;              // the group's instances
   unsigned* flag = pa.flags + (size_t)grp * pa.nt;
-  unsigned* lost = pa.shake + PS_LOST;
+  const PsBound bound{pa.shake + PS_HALT, pa.seq, pa.wait_ticks};
   const size_t allpw = (size_t)pa.ng * pa.nt * PT_G, alld = (size_t)pa.nb * pa.nt * NV, allp = (size_t)pa.ng * PT_G * NP;
   // the instances this block leads, spread over the tiles
   unsigned lead = 0u;
@@ -196,7 +197,7 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
   };
   for (int sl = 0; sl < 3; ++sl) clear(t0_, sl);
   if (!ps_handshake(pt_shake_args(pa))) {
-    if (tile == 0 && t0_ < G) a.inst[ids[t0_]].off = 1;
+    if (tile == 0 && t0_ < G && a.inst[ids[t0_]].off == 0) a.inst[ids[t0_]].off = PS_OFF;
     return;
   }
   const int64_t N = a.op.N;
@@ -306,7 +307,7 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
     const int lo = (int)(base - h < 0 ? 0 : (base - h) / pa.rows);
     const int hi = (int)min((int64_t)pa.nt - 1, (base + rows - 1 + h) / pa.rows);
     bool f = true;
-    for (int q = lo + t; q <= hi; q += PT_TB) f = ps_wait_ge(flag + q, step, lost) && f;
+    for (int q = lo + t; q <= hi; q += PT_TB) f = ps_wait_ge(flag + q, step, bound) && f;
     if (!f) s_bad = 1;
     __syncthreads();
     ok = !s_bad;
@@ -529,10 +530,7 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
             for (int u = 0; u < 8; ++u) wait |= b[u] == PS_EMPTY;
             if (wait && (++n & 63) == 0) {
               if (n == 64) c0 = wall_clock64();
-              if (ld_agent(lost) != 0u || wall_clock64() - c0 > PS_WAIT_TICKS) {
-                st_agent(lost, 1u);
-                ok = wait = false;
-              }
+              if (bound.lost(c0)) ok = wait = false;
             }
           }
 #pragma unroll
@@ -746,10 +744,7 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
             for (int u = 0; u < U; ++u) wait |= b[u] == PS_EMPTY;
             if (wait && (++n & 63) == 0) {
               if (n == 64) c0 = wall_clock64();
-              if (ld_agent(lost) != 0u || wall_clock64() - c0 > PS_WAIT_TICKS) {
-                st_agent(lost, 1u);
-                ok = wait = false;
-              }
+              if (bound.lost(c0)) ok = wait = false;
             }
           }
 #pragma unroll
@@ -817,7 +812,7 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
       for (int e = t; e < G * NP; e += PT_TB) {
         const int li = e / NP, v = e - li * NP;
         if (!s_live[li]) continue;
-        const double b = pt_take(pub + e, lost, ok);
+        const double b = pt_take(pub + e, bound, ok);
         if (v < KP) cfs[li][v] = b;
         else if (v == KP) s_beta[li] = b;
         else if (v == KP + 1) s_rho[li] = b;
@@ -861,9 +856,9 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
       S->capped = s_cap[i]; S->has_dir = s_dir[i]; S->status = s_stat[i];
       if (s_done[i]) S->done = 1;
       if (s_done[i] == 2) S->outer_done = 1;
-      if (!ok) S->off = 2;
     }
   }
+  if (!ok && t0_ < G) a.inst[ids[t0_]].off = PS_LOST;
 }
 
 }  // namespace adef2

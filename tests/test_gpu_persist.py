@@ -208,3 +208,30 @@ def test_breakdown_stays_in_its_instance(lib):
     for m in range(1, B):
         # both solve to a relative residual of tol, cond(S) <= 3e5
         assert np.linalg.norm(x1[m] - x0[m]) <= 2 * 3e5 * tol * np.linalg.norm(x0[m]), m
+
+
+# 16 tiles an instance; groups of 16, listed rows through LDS; FP32 vectors
+@pytest.mark.parametrize("prec,n,k,B,form", [("fp64", 63, 16, 2, 1), ("mixed", 91, 8, 57, 2), ("fp32", 63, 8, 3, 1)])
+def test_a_wait_that_is_given_up_costs_time_only(lib, prec, n, k, B, form):
+    """Blocks that give up their first wait (bound 0) leave instances with vectors
+    of different iterations: the solve starts again with a kernel per step, whatever
+    the launches queued behind did, and the next solve runs chunk launches again."""
+    w = gen.c2_workload(n=n, k=k, B=B)
+    masks = np.stack([i.mask for i in w.instances])
+    bs = np.stack([i.b for i in w.instances])
+    case(f"waits given up, {prec} cd2d n={n} k={k} B={B}")
+    s = solver(lib, w.op, w.Z, "factored",
+               precision=dict(fp64=lib.FP64, mixed=lib.MIXED_REFINE, fp32=lib.FP32_REFINE)[prec])
+    tol = 1e-8
+    S = spec(w.op, "factored")
+    for bound, from_launch in ((0, 0), (0, 3), (-1, 0)):
+        s.set_chunk_bounds(wait_us=bound, from_launch=from_launch)
+        lost = s.chunk_variant()["lost"] if from_launch or bound else 0
+        out = s.solve_batched(masks, bs, tol)
+        v = s.chunk_variant()
+        print(f"   bound {bound} from launch {from_launch}: {v}", flush=True)
+        if bound == 0:
+            assert v["lost"] == lost + 1 and v["launches"] == 0 and v["form"] == 0
+        else:
+            assert v["lost"] == lost and v["launches"] > 0 and v["form"] == form
+        _check(lib, w, S, out, prec, (0, B - 1), tol)
