@@ -103,7 +103,7 @@ _sig = {
     "adef2_variant": (ctypes.c_int, [_P, _Pi32, _Pi32, _P]),
     "adef2_operator_variant": (ctypes.c_int, [_P, _Pi32, _Pi32, _Pi32, _P]),
     "adef2_update_variant": (ctypes.c_int, [_P, _Pi32, _Pi32, _P]),
-    "adef2_chunk_variant": (ctypes.c_int, [_P, _Pi32, _Pi32, _Pi64, _Pi64]),
+    "adef2_chunk_variant": (ctypes.c_int, [_P, _Pi32, _Pi32, _Pi64, _Pi64, _Pi64]),
     "adef2_set_chunk_bounds": (ctypes.c_int, [_P, _i64, _i64, _i32]),
     "adef2_active_set_batched": (ctypes.c_int, [_P, _i32, _P, _P, _f64, _f64, _i32, _P, _P, _P, _P, _P]),
     "adef2_pod_enrich": (ctypes.c_int, [_P, _i32, _f64]),
@@ -451,11 +451,12 @@ class Solver:
     def chunk_variant(self) -> dict:
         """Chunk launches of the last solve: form (0 none, 1 one instance per
         block, 2 groups of 16) and rows per block of the first, their number,
-        and the context's solves in which a block gave up a wait."""
-        f, r, n, lost = _i32(0), _i32(0), _i64(0), _i64(0)
+        and the context's solves in which a launch was called off and in which a
+        block gave up a wait."""
+        f, r, n, off, lost = _i32(0), _i32(0), _i64(0), _i64(0), _i64(0)
         self._check(_lib.adef2_chunk_variant(self._ctx, ctypes.byref(f), ctypes.byref(r), ctypes.byref(n),
-                                             ctypes.byref(lost)), allow=(OK,))
-        return dict(form=f.value, rows=r.value, launches=n.value, lost=lost.value)
+                                             ctypes.byref(off), ctypes.byref(lost)), allow=(OK,))
+        return dict(form=f.value, rows=r.value, launches=n.value, called_off=off.value, lost=lost.value)
 
     def set_chunk_bounds(self, handshake_us=-1, wait_us=-1, from_launch=0):
         """Bounds of the chunk launches' handshake and waits (-1: default)."""

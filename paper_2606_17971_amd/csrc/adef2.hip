@@ -63,6 +63,7 @@ constexpr double EIG_TOL = 1e-6;
 // shared in time slices.
 constexpr int64_t PS_SHAKE_US = 20000, PS_WAIT_US = 4000000;
 constexpr int RC_REDO = -1000;                 // (internal) solve again without chunk launches
+constexpr int PS_SKIP_MAX = 64;
 constexpr double FP32_COND = 1e-3 / 5.96e-8;   // learned cond(E) bound with FP32 panels
 
 enum KernelId { KI_INIT = 0, KI_INIT2, KI_PUPDATE, KI_SPMV, KI_UPDATE, KI_RESID, KI_ACCUM,
@@ -243,9 +244,12 @@ struct adef2_ctx {
   // solve on (before it the defaults are)
   int64_t ps_shake_us = PS_SHAKE_US, ps_wait_us = PS_WAIT_US;
   int ps_from = 0;
-  bool no_chunk = false;         // this solve runs without chunk launches
+  bool no_chunk = false;         // this solve (or what is left of it) runs without chunk launches
+  // after a solve that stepped back: solves to leave without chunk launches, and
+  // how many that were the last time (0: the last chunk launches went through)
+  int ps_skip = 0, ps_back = 0;
   // the last solve's chunk launches: how many, and the first one's form and rows
-  int64_t ch_launches = 0, ch_lost = 0;
+  int64_t ch_launches = 0, ch_lost = 0, ch_off = 0;
   int ch_form = 0, ch_rows = 0;
   // persistent tile-major chunk kernel (k_persist_tm): steps its registers are
   // laid out for (0: not in use), steps and rows per tile; rows of 16 instances
@@ -1314,6 +1318,16 @@ bool persist_plan(adef2_ctx* c) {
   return c->ps_rows > 0 || persist_tm_plan(c);
 }
 
+// A solve steps back from its chunk launches.  What made it (another context's
+// launches, other work on the GPU) usually goes on for a while, and finding out
+// again costs the handshake's 20 ms: the next 2 solves run a kernel per step, twice
+// as many each further time without a solve that went through.
+void persist_step_back(adef2_ctx* c) {
+  c->no_chunk = true;
+  c->ps_back = std::min(PS_SKIP_MAX, std::max(2, 2 * c->ps_back));
+  c->ps_skip = c->ps_back;
+}
+
 // Takes the instances that still iterate (all: every one) as the list of the
 // persistent kernels' next launches and plans for them; persist: whether one
 // applies.  The stream is idle when the list changes.
@@ -1518,23 +1532,30 @@ int run_sweep(adef2_ctx* c, const double* src, const double* x0pad, double thres
   const int pmax = std::max(1, c->o.poll_max);
   std::vector<double> prev_rr(c->B, 0.0);
   std::vector<int> prev_it(c->B, -1);
-  int64_t launched = 0;
+  int64_t launched = 0, queued = 0;           // iterations, and those since the last poll
   for (;;) {
     bool ad = false;
     int rc = poll(c, b_outer != nullptr, &ad);
     if (rc) return rc;
     if (persist) {
       // a chunk that was called off (not every block got a compute unit in
-      // time) has changed nothing: go on with one kernel per step.  A block that
-      // gave up a wait leaves the instance's vectors of different iterations:
-      // start again
+      // time) and those queued behind it have changed nothing: go on with one
+      // kernel per step, or start again with the tuned ones when nothing was
+      // done yet.  A block that gave up a wait leaves the instance's vectors of
+      // different iterations: start again
       int off = 0;
-      for (int m = 0; m < c->B; ++m) off = std::max(off, (int)c->inst_h[m].off);
-      if (off == PS_LOST) {
-        ++c->ch_lost;
-        return RC_REDO;
+      int it = 0;
+      for (int m = 0; m < c->B; ++m) {
+        off = std::max(off, (int)c->inst_h[m].off);
+        it = std::max(it, (int)c->inst_h[m].iters);
       }
-      if (off == PS_OFF) persist = may_persist = false;
+      if (off) {
+        ++(off == PS_LOST ? c->ch_lost : c->ch_off);
+        persist_step_back(c);
+        if (off == PS_LOST || it == 0) return RC_REDO;
+        persist = may_persist = false;
+        launched -= queued;
+      }
     }
     if (ad) break;
     // fewer instances may fit where all did not, or need fewer tiles or groups
@@ -1562,6 +1583,7 @@ int run_sweep(adef2_ctx* c, const double* src, const double* x0pad, double thres
     // residuals do not predict: poll_max chunks between polls
     int nrep = b_outer ? pmax : (int)std::min<double>((double)pmax, std::max(1.0, std::floor(0.5 * est / chunk)));
     if (max_chunks > 0) nrep = std::min<int64_t>(nrep, std::max<int64_t>(1, max_chunks - launched / chunk));
+    queued = (int64_t)nrep * chunk;
     for (int rep = 0; rep < nrep; ++rep) {
       launched += chunk;
       if (c->o.profile) bm = byte_model(c, (double)sizeof(V), (double)sizeof(M), true);
@@ -1623,10 +1645,24 @@ int choose_variant(adef2_ctx* c, const double* b) {
                 "the tile-major boundary-form update needs FP32 panels with FP64 vectors (MIXED_REFINE), "
                 "reference modes shared by all instances that are eigenvectors of the reference operator, "
                 "and w_boundary enabled");
+  const int fact = c->factored ? 1 : 0, tmk = c->tm_ok ? 1 : 0;
+  const int fu = c->o.update_ws;
+  const int opo = fo + 4 * c->o.op_group + 32 * c->o.op_rows;   // the operator options tuned under
+  auto use_tuned = [&]() {
+    for (const auto& t : c->tuned)
+      if (t.B == c->B && t.prec == c->prec && t.KP == c->KP && t.fact == fact && t.tm == tmk &&
+          t.N == c->N && t.opo == opo && t.uwo == fu && t.fro == fr && t.fwo == fw) {
+        set_variant(c, t.rpt, t.wfree, t.opf, t.opg, t.uws);
+        return true;
+      }
+    return false;
+  };
   c->nlive = c->B;
   if (!c->no_chunk && persist_plan(c)) {
-    // (the variant of the kernel-per-step form, in case a chunk is called off)
-    set_variant(c, 2, c->tm_ok ? 3 : persist_form(c) == PS_FREE ? 2 : 0, opf_default_rows(c));
+    // the variant of the kernel-per-step form stands by, in case a chunk is called
+    // off half-way: the tuned one if there is one
+    if (!use_tuned())
+      set_variant(c, 2, c->tm_ok ? 3 : persist_form(c) == PS_FREE ? 2 : 0, opf_default_rows(c));
     return ADEF2_OK;
   }
   // fused operator pass: the (tile height, instances per block) candidates
@@ -1671,7 +1707,6 @@ int choose_variant(adef2_ctx* c, const double* b) {
   const int op0 = fo == 1 ? R1 : 0, og0 = fo == 1 ? G1 : 1;
   // update form of the tile-major path: per tile (k_update_tm) or
   // warp-specialised runs of tiles (k_update_ws, up to 32 modes)
-  const int fu = c->o.update_ws;
   const bool ws_ok = c->tm_ok && c->KP > 0 && c->KP <= 32 && vec64(c->prec);
   if (fu == 1 && !ws_ok)
     return fail(c, ADEF2_E_UNSUPPORTED,
@@ -1682,15 +1717,7 @@ int choose_variant(adef2_ctx* c, const double* b) {
     set_variant(c, rpts[0], wfs[0], op0, og0, uw0);
     return ADEF2_OK;
   }
-  const int fact = c->factored ? 1 : 0;
-  const int tmk = c->tm_ok ? 1 : 0;
-  const int opo = fo + 4 * c->o.op_group + 32 * c->o.op_rows;   // the operator options tuned under
-  for (const auto& t : c->tuned)
-    if (t.B == c->B && t.prec == c->prec && t.KP == c->KP && t.fact == fact && t.tm == tmk &&
-        t.N == c->N && t.opo == opo && t.uwo == fu && t.fro == fr && t.fwo == fw) {
-      set_variant(c, t.rpt, t.wfree, t.opf, t.opg, t.uws);
-      return ADEF2_OK;
-    }
+  if (use_tuned()) return ADEF2_OK;
   const int prof = c->o.profile;
   c->o.profile = 0;
   hipEvent_t e0, e1;
@@ -1763,7 +1790,8 @@ int choose_variant(adef2_ctx* c, const double* b) {
   return ADEF2_OK;
 }
 
-// One attempt at solve_batch: RC_REDO when a chunk launch gave up a wait
+// One attempt at solve_batch: RC_REDO when it has to be made again without chunk
+// launches
 int solve_once(adef2_ctx* c, const double* b, const double* x0, double tol, double* x, const double* tols) {
   const int B = c->B;
   const int64_t N = c->N;
@@ -1854,16 +1882,15 @@ int solve_once(adef2_ctx* c, const double* b, const double* x0, double tol, doub
 // (x is written last, so a second attempt starts from the same inputs.)
 int solve_batch(adef2_ctx* c, const double* b, const double* x0, double tol, double* x,
                 const double* tols = nullptr) {
-  c->no_chunk = false;
-  c->ch_launches = 0;
-  c->ch_form = c->ch_rows = 0;
-  int rc = solve_once(c, b, x0, tol, x, tols);
-  if (rc == RC_REDO) {
-    c->no_chunk = true;
+  c->no_chunk = c->ps_skip > 0;
+  if (c->no_chunk) --c->ps_skip;
+  int rc = RC_REDO;
+  while (rc == RC_REDO) {          // (the second attempt runs without chunk launches)
     c->ch_launches = 0;
     c->ch_form = c->ch_rows = 0;
     rc = solve_once(c, b, x0, tol, x, tols);
   }
+  if (rc == ADEF2_OK && c->ch_launches > 0 && !c->no_chunk) c->ps_back = 0;
   return rc;
 }
 
@@ -2693,15 +2720,18 @@ int adef2_set_chunk_bounds(adef2_ctx* c, int64_t handshake_us, int64_t wait_us, 
   c->ps_shake_us = handshake_us < 0 ? PS_SHAKE_US : handshake_us;
   c->ps_wait_us = wait_us < 0 ? PS_WAIT_US : wait_us;
   c->ps_from = from_launch;
+  c->ps_skip = c->ps_back = 0;
   return ADEF2_OK;
 }
 
-int adef2_chunk_variant(adef2_ctx* c, int32_t* form, int32_t* rows, int64_t* launches, int64_t* lost) {
+int adef2_chunk_variant(adef2_ctx* c, int32_t* form, int32_t* rows, int64_t* launches, int64_t* called_off,
+                        int64_t* lost) {
   if (!c) return ADEF2_E_ARG;
   if (!c->solved) return fail(c, ADEF2_E_STATE, "chunk_variant before the first solve");
   if (form) *form = c->ch_form;
   if (rows) *rows = c->ch_rows;
   if (launches) *launches = c->ch_launches;
+  if (called_off) *called_off = c->ch_off;
   if (lost) *lost = c->ch_lost;
   return ADEF2_OK;
 }

@@ -235,3 +235,57 @@ def test_a_wait_that_is_given_up_costs_time_only(lib, prec, n, k, B, form):
         else:
             assert v["lost"] == lost and v["launches"] > 0 and v["form"] == form
         _check(lib, w, S, out, prec, (0, B - 1), tol)
+
+
+@pytest.mark.parametrize("prec,n,k,B", [("fp64", 63, 16, 2), ("mixed", 91, 8, 57), ("fp32", 63, 8, 3)])
+def test_called_off_launches_step_back(lib, prec, n, k, B):
+    """A chunk launch that is called off (bound 0) leaves its solve to the kernels per
+    step: the tuned ones when it is the first launch, from where the solve is when it
+    is a later one. The next solves remember it."""
+    w = gen.c2_workload(n=n, k=k, B=B)
+    masks = np.stack([i.mask for i in w.instances])
+    bs = np.stack([i.b for i in w.instances])
+    case(f"chunk launches called off, {prec} cd2d n={n} k={k} B={B}")
+    tol = 1e-8
+    S = spec(w.op, "factored")
+    per_step = ("pupdate", "pupdate_bt", "pupdate_tm")
+    for from_launch in (0, 3):
+        s = solver(lib, w.op, w.Z, "factored", profile=1,
+                   precision=dict(fp64=lib.FP64, mixed=lib.MIXED_REFINE, fp32=lib.FP32_REFINE)[prec])
+        s.set_chunk_bounds(handshake_us=0, from_launch=from_launch)
+        out = s.solve_batched(masks, bs, tol)
+        v, st = s.chunk_variant(), s.stats()
+        print(f"   from launch {from_launch}: {v}, trial ms {s.variant()[2].max():.2f}", flush=True)
+        assert v["called_off"] == 1 and v["lost"] == 0
+        assert sum(st[q]["launches"] for q in per_step) > 0
+        assert (v["launches"] == 0) == (from_launch == 0)
+        assert (s.variant()[2].max() > 0) == (from_launch == 0)      # tuned
+        _check(lib, w, S, out, prec, (0, B - 1), tol)
+        # two solves without a try, one that tries, then four
+        tries = []
+        for _ in range(7):
+            s.solve_batched(masks, bs, 1e-2)
+            tries.append(s.chunk_variant()["called_off"])
+        if from_launch == 0:
+            assert tries == [1, 1, 2, 2, 2, 2, 2], tries
+        s.set_chunk_bounds()
+        out = s.solve_batched(masks, bs, tol)
+        assert s.chunk_variant()["form"] > 0
+        _check(lib, w, S, out, prec, (0, B - 1), tol)
+
+
+@pytest.mark.parametrize("from_launch", [0, 1, 2])
+def test_called_off_launches_and_the_iteration_cap(lib, from_launch):
+    """The launches queued behind one that is called off are no iterations: a
+    refinement solve that reaches its cap says so."""
+    w = gen.c2_workload(n=63, k=8, B=3)
+    masks = np.stack([i.mask for i in w.instances])
+    bs = np.stack([i.b for i in w.instances])
+    case(f"called off at launch {from_launch}, then the iteration cap")
+    s = solver(lib, w.op, w.Z, "factored", precision=lib.MIXED_REFINE, maxit=150, segment_maxit=5)
+    s.set_chunk_bounds(handshake_us=0, from_launch=from_launch)
+    out = s.solve_batched(masks, bs, 1e-10)
+    v = s.chunk_variant()
+    print(f"   {v} iters {out['iters']}", flush=True)
+    assert v["called_off"] == 1
+    assert np.all(out["status"] == lib.W_MAXIT) and np.all(out["iters"] == 150)
