@@ -581,24 +581,25 @@ int adef2_update_variant(adef2_ctx *ctx, int32_t *warp_specialised, int32_t *til
 /* Chunk launches (persistent kernels, see opts.check_every) of the last solve on
  * ctx: form of the first one (0: none, the solve ran a kernel per step; 1: one
  * instance per block; 2: groups of 16 instances), its rows per block and the
- * number of launches.  called_off, lost: solves of this context in which a launch
- * was called off and in which a block gave up a wait (see adef2_set_chunk_bounds).
- * Any pointer may be NULL.  E_STATE before the first solve. */
+ * number of launches.
+ * A launch needs all of its blocks on the GPU at once.  When other work holds
+ * compute units and they have not all started after 20 ms, it is called off before
+ * it changes anything, and the solve goes on with a kernel per step (the tuned
+ * ones, if it was the first launch or an earlier solve has tuned them).  When a
+ * block has waited 4 s for another one, it gives the launch up, and the solve
+ * starts again with a kernel per step.  After either the context's next 2 solves
+ * make no chunk launches, then one tries again (4 the next time, up to 64, until
+ * one goes through).  called_off, lost: solves of this context to which the one
+ * and the other happened.  Any pointer may be NULL.  E_STATE before the first
+ * solve. */
 int adef2_chunk_variant(adef2_ctx *ctx, int32_t *form, int32_t *rows, int64_t *launches, int64_t *called_off,
                         int64_t *lost);
 
-/* Bounds of the chunk launches' waits, for a GPU that is shared with other work;
- * < 0: the default.  handshake_us (20 ms): a launch whose blocks have not all
- * started within it is called off before it changes anything, and the solve goes
- * on with a kernel per step (the tuned ones, if it was the first launch or an
- * earlier solve has tuned them); 0: every launch is called off.  wait_us (4 s): a
- * block that waits longer for another one gives the launch up, and the solve
- * starts again with a kernel per step; 0: the first wait that is not over at once.
- * After either the context's next 2 solves make no chunk launches, then one tries
- * again (4 the next time, up to 64); this call forgets that.  from_launch: the
- * chunk launch of a solve (from 0) from which on the two bounds hold; before it the
- * defaults do.  At most 1e9 us each (E_ARG). */
-int adef2_set_chunk_bounds(adef2_ctx *ctx, int64_t handshake_us, int64_t wait_us, int32_t from_launch);
+/* For tests: what goes wrong with the chunk launches of the next solves, from
+ * launch from_launch (>= 0) of a solve on.  kind 1: they are called off; 2: blocks
+ * start 1 ms late and those that wait for them give up; 0: nothing.  Also forgets
+ * earlier call-offs (see adef2_chunk_variant). */
+int adef2_chunk_fault(adef2_ctx *ctx, int32_t kind, int32_t from_launch);
 
 #define ADEF2_STATS_KERNELS 24
 typedef struct {

@@ -57,13 +57,10 @@ constexpr double FP32_DROP = 1e-3;   // column-drop threshold with FP32 panels
 // the order of the FP32 rounding (6e-8) of the stored W that the mixed
 // iteration carries anyway; the FP64 residual replacement keeps the accuracy
 constexpr double EIG_TOL = 1e-6;
-// Bounds of the persistent chunk kernels: blocks of a launch that fits an idle GPU
-// start within microseconds, so 20 ms means that other work holds compute units;
-// a wait is an iteration of another block (10-200 us), 4 s allow for a GPU that is
-// shared in time slices.
-constexpr int64_t PS_SHAKE_US = 20000, PS_WAIT_US = 4000000;
 constexpr int RC_REDO = -1000;                 // (internal) solve again without chunk launches
 constexpr int PS_SKIP_MAX = 64;
+constexpr size_t INST_OFS = 512;               // bytes of the handshake words before the instances
+static_assert(PS_WORDS * sizeof(unsigned) <= INST_OFS && INST_OFS % alignof(Inst) == 0, "");
 constexpr double FP32_COND = 1e-3 / 5.96e-8;   // learned cond(E) bound with FP32 panels
 
 enum KernelId { KI_INIT = 0, KI_INIT2, KI_PUPDATE, KI_SPMV, KI_UPDATE, KI_RESID, KI_ACCUM,
@@ -176,7 +173,11 @@ struct adef2_ctx {
   int* cofs = nullptr;
   long long* ntot = nullptr;
   Inst* inst = nullptr;
-  Inst* inst_h = nullptr;        // pinned mirror
+  Inst* inst_h = nullptr;        // pinned mirror (in ps_shake_h)
+  // the words of the chunk launches' handshake and, INST_OFS bytes on, inst: the
+  // host reads both at once
+  unsigned char* inst_mem = nullptr;
+  unsigned *ps_shake = nullptr, *ps_shake_h = nullptr;
   double* C = nullptr;
   double* Finfo = nullptr;
   int* kept = nullptr;
@@ -236,14 +237,10 @@ struct adef2_ctx {
   int n_cu = 0;
   unsigned* ps_flags = nullptr;
   double *ps_pw = nullptr, *ps_dots = nullptr;
-  unsigned* ps_shake = nullptr;
   size_t ps_tiles = 0, ps_vals = 0;   // tiles, and tiles times values, allocated
   unsigned ps_seq = 0, ps_base = 0;
   bool ps_ready = false;         // handshake words cleared for this sequence of launches
-  // bounds of the handshake and of a wait in us, kept from launch ps_from of a
-  // solve on (before it the defaults are)
-  int64_t ps_shake_us = PS_SHAKE_US, ps_wait_us = PS_WAIT_US;
-  int ps_from = 0;
+  int ps_fault = 0, ps_from = 0; // tests: what goes wrong, from which launch of a solve on
   bool no_chunk = false;         // this solve (or what is left of it) runs without chunk launches
   // after a solve that stepped back: solves to leave without chunk launches, and
   // how many that were the last time (0: the last chunk launches went through)
@@ -359,19 +356,19 @@ void free_all(adef2_ctx* c) {
   if (c->gst) { hipStreamDestroy(c->gst); c->gst = nullptr; }
   auto F = [](void* p) { if (p) hipFree(p); };
   F(c->dia64); F(c->dia32); F(c->diag); F(c->Z64); F(c->Z32);
-  F(c->masks); F(c->I); F(c->g2l); F(c->ccount); F(c->cofs); F(c->ntot); F(c->inst);
+  F(c->masks); F(c->I); F(c->g2l); F(c->ccount); F(c->cofs); F(c->ntot); F(c->inst_mem);
   F(c->C); F(c->Finfo); F(c->kept); F(c->gram);
   for (int j = 0; j < 5; ++j) { F(c->v64[j]); F(c->v32[j]); }
   F(c->W64); F(c->W32); F(c->dinv64); F(c->dinv32); F(c->x64); F(c->r64); F(c->x0pad);
   F(c->t64); F(c->t32); F(c->Tm); F(c->dia1_64); F(c->dia1_32);
   F(c->part); F(c->ctr);
-  F(c->ps_flags); F(c->ps_pw); F(c->ps_dots); F(c->ps_shake); F(c->live_d);
+  F(c->ps_flags); F(c->ps_pw); F(c->ps_dots); F(c->live_d);
   F(c->pt_P); F(c->pt_T); F(c->pt_Q); F(c->pt_X); F(c->pt_D); F(c->pt_flags); F(c->pt_pw); F(c->pt_dots); F(c->pt_pub);
   F(c->Phi); F(c->mlp); F(c->mlp_bf); F(c->mlp_g); F(c->mlp_part); F(c->mlp_m); F(c->mlp_v); F(c->theta_tr);
   F(c->Htr); F(c->Ntr); F(c->gtr); F(c->e0tr); F(c->bxtr); F(c->act); F(c->mout); F(c->dout); F(c->dA1);
   F(c->dA2); F(c->lossv); F(c->Zb64); F(c->Zb32); F(c->mu64); F(c->eigf); F(c->bnd); F(c->hb); F(c->zero64);
   F(c->ZT32); F(c->bcnt); F(c->ftot); F(c->fctr); F(c->btoff); F(c->btot); F(c->bidx); F(c->bW32);
-  if (c->inst_h) hipHostFree(c->inst_h);
+  if (c->ps_shake_h) hipHostFree(c->ps_shake_h);
   for (auto& e : c->ev_pending) { hipEventDestroy(e.a); hipEventDestroy(e.b); }
   for (auto e : c->ev_pool) hipEventDestroy(e);
 }
@@ -597,10 +594,15 @@ int ensure_batch(adef2_ctx* c, int B, int prec) {
   if ((rc = dalloc(c, &c->ccount, (size_t)B * nchunks))) return rc;
   if ((rc = dalloc(c, &c->cofs, (size_t)B * nchunks))) return rc;
   if ((rc = dalloc(c, &c->ntot, (size_t)B))) return rc;
-  if ((rc = dalloc(c, &c->inst, (size_t)B))) return rc;
-  if (c->inst_h) hipHostFree(c->inst_h);
+  c->inst = nullptr;
+  if ((rc = dalloc(c, &c->inst_mem, INST_OFS + sizeof(Inst) * B))) return rc;
+  c->ps_shake = (unsigned*)c->inst_mem;
+  c->inst = (Inst*)(c->inst_mem + INST_OFS);
+  if (c->ps_shake_h) hipHostFree(c->ps_shake_h);
+  c->ps_shake_h = nullptr;
   c->inst_h = nullptr;
-  HIPCHK(c, hipHostMalloc((void**)&c->inst_h, sizeof(Inst) * B));
+  HIPCHK(c, hipHostMalloc((void**)&c->ps_shake_h, INST_OFS + sizeof(Inst) * B));
+  c->inst_h = (Inst*)((char*)c->ps_shake_h + INST_OFS);
   const size_t kk = (size_t)std::max(KP, 1) * std::max(KP, 1);
   if ((rc = dalloc(c, &c->C, (size_t)B * kk))) return rc;
   if ((rc = dalloc(c, &c->Finfo, (size_t)B * kk))) return rc;
@@ -920,7 +922,7 @@ ByteModel byte_model(const adef2_ctx* c, double wv, double wm, bool sweep_active
 
 int poll(adef2_ctx* c, bool outer, bool* all_done) {
   c->st_polls += 1;
-  HIPCHK(c, hipMemcpyAsync(c->inst_h, c->inst, sizeof(Inst) * c->B, hipMemcpyDeviceToHost, c->st));
+  HIPCHK(c, hipMemcpyAsync(c->ps_shake_h, c->ps_shake, INST_OFS + sizeof(Inst) * c->B, hipMemcpyDeviceToHost, c->st));
   HIPCHK(c, hipStreamSynchronize(c->st));
   bool ad = true;
   for (int m = 0; m < c->B; ++m) {
@@ -1110,30 +1112,33 @@ int persist_rows(adef2_ctx* c) {
   return 0;
 }
 
-// words of the handshake, cleared once per sequence of launches (a launch that
-// was halted in an earlier one leaves the halt word set)
-int persist_shake(adef2_ctx* c) {
-  int rc;
-  if (!c->ps_shake && (rc = dalloc(c, &c->ps_shake, PS_WORDS))) return rc;
-  if (!c->ps_ready) {
-    fill<unsigned>(c, c->ps_shake, PS_WORDS, 0u);
-    c->ps_seq = c->ps_base = 0;
-    c->ps_ready = true;
-  }
-  return ADEF2_OK;
+// clears the words of the handshake, once per sequence of launches (a launch that
+// was halted in an earlier one leaves them set)
+void persist_shake(adef2_ctx* c) {
+  if (c->ps_ready) return;
+  fill<unsigned>(c, c->ps_shake, PS_WORDS, 0u);
+  c->ps_seq = 1;
+  c->ps_base = 0;
+  c->ps_ready = true;
 }
 
-// Bounds and number of the next launch of nblk blocks
+// Number of the next launch, of nblk blocks
 template <typename Args>
 void persist_launch_args(adef2_ctx* c, Args& pa) {
-  const bool own = c->ch_launches >= c->ps_from;
-  const int64_t sh = own ? c->ps_shake_us : PS_SHAKE_US, wt = own ? c->ps_wait_us : PS_WAIT_US;
   pa.shake = c->ps_shake;
-  pa.shake_ticks = sh > 0 ? sh * PS_TICKS_US : -1;
-  pa.wait_ticks = wt > 0 ? wt * PS_TICKS_US : -1;
   pa.seq = ++c->ps_seq;
   pa.base = c->ps_base;
   c->ps_base += pa.nblk;
+  if (c->ps_fault && c->ch_launches >= c->ps_from) {
+    if (c->ps_fault == 1) {
+      ++pa.nblk;                 // one block more than the grid has: not all arrive
+    } else {
+      pa.stall = 100000;          // 1 ms of the 100 MHz counter
+      if (c->ch_launches == c->ps_from)
+        hipLaunchKernelGGL(k_fill<unsigned>, dim3(1), dim3(64), 0, c->st, c->ps_shake + PS_LOST, (int64_t)1,
+                           (unsigned)PS_GIVE_UP);
+    }
+  }
   if (c->ch_launches++ == 0) {
     c->ch_form = c->pt_e ? 2 : 1;
     c->ch_rows = c->pt_e ? c->pt_rows : c->ps_rows;
@@ -1146,7 +1151,7 @@ int persist_buffers(adef2_ctx* c) {
   const size_t tiles = std::max((size_t)cdiv(c->N, (int64_t)c->ps_rows) * c->nlive, 2 * (size_t)c->n_cu);
   const size_t vals = tiles * (2 * c->KP + 2);
   int rc;
-  if ((rc = persist_shake(c))) return rc;
+  persist_shake(c);
   if (tiles > c->ps_tiles) {
     c->ps_tiles = 0;
     if ((rc = dalloc(c, &c->ps_flags, tiles)) || (rc = dalloc(c, &c->ps_pw, 3 * tiles))) return rc;
@@ -1279,7 +1284,8 @@ int persist_tm_buffers(adef2_ctx* c) {
     if ((rc = dalloc(c, &c->pt_pub, 3 * pubs))) return rc;
     c->pt_pubs = pubs;
   }
-  return persist_shake(c);
+  persist_shake(c);
+  return ADEF2_OK;
 }
 
 void launch_persist_tm(adef2_ctx* c, const IterArgs<double, float>& a, int chunk, hipStream_t s) {
@@ -1543,16 +1549,14 @@ int run_sweep(adef2_ctx* c, const double* src, const double* x0pad, double thres
       // kernel per step, or start again with the tuned ones when nothing was
       // done yet.  A block that gave up a wait leaves the instance's vectors of
       // different iterations: start again
-      int off = 0;
-      int it = 0;
-      for (int m = 0; m < c->B; ++m) {
-        off = std::max(off, (int)c->inst_h[m].off);
-        it = std::max(it, (int)c->inst_h[m].iters);
-      }
-      if (off) {
-        ++(off == PS_LOST ? c->ch_lost : c->ch_off);
+      const unsigned dec = c->ps_shake_h[PS_DECISION];
+      const bool lost = c->ps_shake_h[PS_LOST] == 1, off = dec != 0 && dec % 2 == 0;
+      if (lost || off) {
+        ++(lost ? c->ch_lost : c->ch_off);
         persist_step_back(c);
-        if (off == PS_LOST || it == 0) return RC_REDO;
+        int it = 0;
+        for (int m = 0; m < c->B; ++m) it = std::max(it, (int)c->inst_h[m].iters);
+        if (lost || it == 0) return RC_REDO;
         persist = may_persist = false;
         launched -= queued;
       }
@@ -1617,7 +1621,7 @@ int reset_solve_state(adef2_ctx* c) {
     Inst& s = c->inst_h[m];
     s.iters = 0; s.sweep_iters = 0; s.done = 0; s.outer_done = 0; s.status = 0; s.sweeps = 0;
     s.has_dir = 0; s.rho_end = 0.0; s.stall = 0; s.rr64_best = INFINITY; s.drift = 0;
-    s.capped = 0; s.trans = 0; s.off = 0;
+    s.capped = 0; s.trans = 0;
     s.rr = 0; s.rr64 = 0; s.bb64 = 0;
     const double t = m < (int)c->tol_h.size() ? c->tol_h[m] : 1e-8;
     s.tol2 = t * t;
@@ -2713,12 +2717,10 @@ int adef2_variant(adef2_ctx* c, int32_t* rows_per_thread, int32_t* w_mode, float
   return ADEF2_OK;
 }
 
-int adef2_set_chunk_bounds(adef2_ctx* c, int64_t handshake_us, int64_t wait_us, int32_t from_launch) {
+int adef2_chunk_fault(adef2_ctx* c, int32_t kind, int32_t from_launch) {
   if (!c) return ADEF2_E_ARG;
-  if (handshake_us > 1000000000 || wait_us > 1000000000 || from_launch < 0)
-    return fail(c, ADEF2_E_ARG, "chunk bounds are at most 1e9 us, from_launch at least 0");
-  c->ps_shake_us = handshake_us < 0 ? PS_SHAKE_US : handshake_us;
-  c->ps_wait_us = wait_us < 0 ? PS_WAIT_US : wait_us;
+  if (kind < 0 || kind > 2 || from_launch < 0) return fail(c, ADEF2_E_ARG, "chunk fault 0, 1 or 2, from_launch >= 0");
+  c->ps_fault = kind;
   c->ps_from = from_launch;
   c->ps_skip = c->ps_back = 0;
   return ADEF2_OK;

@@ -28,9 +28,8 @@
 // the device, and begins with a handshake: a block that does not see all of
 // them arrive in time (other work may hold compute units) calls the launch
 // off; nothing has been changed then and the host goes on with one kernel per
-// step.  Waits after the handshake are bounded too: a block that gives one up
-// marks its instances, and the host solves again with one kernel per step.  The
-// launches queued behind either of the two find the halt word set and do nothing.
+// step.  Waits after the handshake are bounded too: when a block gives one up the
+// host solves again with one kernel per step.
 #pragma once
 #include "dev_kernels.h"
 
@@ -38,25 +37,29 @@ namespace adef2 {
 
 constexpr int PS_TB = 512;              // threads per block
 constexpr int PS_NW = PS_TB / 64;
-constexpr long long PS_TICKS_US = 100;             // wall_clock64 counts at 100 MHz
+constexpr long long PS_SHAKE_TICKS = 2000000;      // 20 ms of the 100 MHz counter
+constexpr long long PS_WAIT_TICKS = 400000000;     // 4 s
 constexpr unsigned long long PS_EMPTY = 0x7FF4A5A55A5A4321ull;   // signalling NaN
 
-// halt: 0, or the number of the launch that was called off or gave up a wait
-enum { PS_ARRIVED = 0, PS_DECISION = 16, PS_HALT = 32, PS_WORDS = 48 };
-enum { PS_OFF = 1, PS_LOST = 2 };       // Inst::off
+// PS_DECISION: 2 seq of the last launch when it was called off, else 2 seq + 1.
+// PS_LOST: 1 when a block gave up a wait (PS_GIVE_UP: none has, but every one is to
+// that waits for long).  The host clears the words, and reads these two where it
+// reads the instances' states.
+enum { PS_ARRIVED = 0, PS_DECISION = 16, PS_LOST = 32, PS_WORDS = 48 };
+enum { PS_GIVE_UP = 2 };
 
 struct PersistArgs {
   unsigned* flags;      // [nb][nt] step counters
   double* pw;           // [3][nb][nt] partial sums of p.w
   double* dots;         // [3][nb][nt][2 KP + 2] partial sums of the update
-  unsigned* shake;      // PS_WORDS words: arrivals, decision, halt
-  unsigned seq;         // number of this launch (from 1)
+  unsigned* shake;      // PS_WORDS words
+  long long stall;      // tests: the first tiles start late by this many ticks
+  unsigned seq;         // number of this launch (from 2: 2 seq - 2 is not 0)
   unsigned base;        // arrivals before this launch
   unsigned nblk;        // blocks that arrive
   int nt;               // tiles of an instance
   const int* ids;       // the instances of this launch (those still iterating), nb of them
   int nb;
-  long long shake_ticks, wait_ticks;   // bounds of the handshake and of a wait (< 0: none is kept)
   int chunk;            // iterations
   int reach1, reach;    // reach of the inner (factored) and of the outer stencil
   int fused;            // the inner product stays in LDS, its halo formed twice
@@ -83,28 +86,17 @@ __device__ __forceinline__ void ps_place(int n, int& tile, int& which) {
   which = id - tile * n;
 }
 
-// Bound of the waits of a launch.  lost: the bound has passed since t0, or another
-// block gave up (past the handshake only this launch sets the halt word).
-struct PsBound {
-  unsigned* halt;
-  unsigned seq;
-  long long ticks;
-  __device__ __forceinline__ bool lost(long long t0) const {
-    if (ld_agent(halt) == 0u && wall_clock64() - t0 <= ticks) return false;
-    st_agent(halt, seq);
-    return true;
-  }
-};
-
 // Poll until *p reaches v (step counters grow); false when the bound passed.
-__device__ __forceinline__ bool ps_wait_ge(const unsigned* p, unsigned v, const PsBound& bound) {
+__device__ __forceinline__ bool ps_wait_ge(const unsigned* p, unsigned v, unsigned* lost) {
   if ((int)(ld_agent(p) - v) >= 0) return true;
   const long long t0 = wall_clock64();
   for (;;) {
-    if (bound.ticks >= 0)
-      for (int i = 0; i < 64; ++i)
-        if ((int)(ld_agent(p) - v) >= 0) return true;
-    if (bound.lost(t0)) return false;
+    for (int i = 0; i < 64; ++i)
+      if ((int)(ld_agent(p) - v) >= 0) return true;
+    if (ld_agent(lost) != 0u || wall_clock64() - t0 > PS_WAIT_TICKS) {
+      st_agent(lost, 1u);
+      return false;
+    }
   }
 }
 
@@ -113,8 +105,8 @@ __device__ __forceinline__ unsigned long long ps_bits(const double* p) {
 }
 
 // Every block of the launch calls this once.  True: all blocks are resident
-// and every one of them was told so.  False: the launch is called off, or it is
-// queued behind one that was halted.
+// and every one of them was told so.  False: the launch is called off, at once if
+// the one before it was.
 __device__ inline bool ps_handshake(const PersistArgs& a) {
   __shared__ int s_go;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -123,31 +115,35 @@ __device__ inline bool ps_handshake(const PersistArgs& a) {
   if (threadIdx.x == 0) {
     unsigned* dec = a.shake + PS_DECISION;
     const unsigned go = 2u * a.seq + 1u, off = 2u * a.seq;
-    const unsigned halt = ld_agent(a.shake + PS_HALT);
-    const bool behind = halt != 0u && halt != a.seq;   // (the same in every block: set by an earlier launch)
     const unsigned old = __hip_atomic_fetch_add(a.shake + PS_ARRIVED, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     unsigned cur = ld_agent(dec);
-    const bool last = old - a.base == a.nblk - 1u && a.shake_ticks >= 0;
+    const bool behind = cur == off - 2u;       // the launch before was called off
+    const bool last = old - a.base == a.nblk - 1u && !behind;
     const long long t0 = wall_clock64();
-    while (!behind && cur != go && cur != off) {
-      const bool late = wall_clock64() - t0 > a.shake_ticks;
+    while (cur != go && cur != off) {
+      const bool late = behind || wall_clock64() - t0 > PS_SHAKE_TICKS;
       if (last || late) {
         unsigned want = cur;
         if (__hip_atomic_compare_exchange_strong(dec, &want, last ? go : off, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT)) {
+                                                 __HIP_MEMORY_SCOPE_AGENT))
           cur = last ? go : off;
-          if (!last) st_agent(a.shake + PS_HALT, a.seq);
-        } else
+        else
           cur = want;
       } else {
         __builtin_amdgcn_s_sleep(1);
         cur = ld_agent(dec);
       }
     }
-    s_go = !behind && cur == go;
+    s_go = cur == go;
   }
   __syncthreads();
   return s_go != 0;
+}
+
+__device__ __forceinline__ void ps_stall(const PersistArgs& a, int tile) {
+  if (a.stall == 0 || tile != 0) return;
+  const long long t0 = wall_clock64();
+  while (wall_clock64() - t0 < a.stall) __builtin_amdgcn_s_sleep(8);
 }
 
 // Sum over the 64 lanes, in every lane: four DPP steps add the 16 lanes of a
@@ -286,7 +282,7 @@ __device__ __forceinline__ int ps_groups(int nt) {
   return g < most ? g : most;
 }
 template <int NV>
-__device__ __forceinline__ double ps_gather(const double* slot, int nt, const PsBound& bound, bool& ok) {
+__device__ __forceinline__ double ps_gather(const double* slot, int nt, unsigned* lost, bool& ok) {
   constexpr int U = PS_U;
   const int G = ps_groups<NV>(nt);
   static_assert(NV <= PS_TB, "one thread per value");
@@ -309,7 +305,10 @@ __device__ __forceinline__ double ps_gather(const double* slot, int nt, const Ps
         for (int u = 0; u < U; ++u) wait |= b[u] == PS_EMPTY;
         if (wait && (++n & 63) == 0) {
           if (n == 64) c0 = wall_clock64();
-          if (bound.lost(c0)) ok = wait = false;
+          if (ld_agent(lost) != 0u || wall_clock64() - c0 > PS_WAIT_TICKS) {
+            st_agent(lost, 1u);
+            ok = wait = false;
+          }
         }
       }
 #pragma unroll
@@ -404,7 +403,7 @@ k_persist(IterArgs<V, M> a, PersistArgs pa) {
   Inst* S = a.inst + m;
   const bool idle = S->done;
   unsigned* flag = pa.flags + (size_t)place * pa.nt;
-  const PsBound bound{pa.shake + PS_HALT, pa.seq, pa.wait_ticks};
+  unsigned* lost = pa.shake + PS_LOST;
   const size_t team = (size_t)place * pa.nt, all = (size_t)pa.nb * pa.nt;
   double rho = S->rho, beta = S->fresh ? 0.0 : S->beta;
   double rr_last = S->rr, pw_last = S->pw, rho_end = S->rho_end;
@@ -423,11 +422,8 @@ k_persist(IterArgs<V, M> a, PersistArgs pa) {
     double* p = v < NV ? pa.dots + (sl * all + team + tile) * NV + v : pa.pw + sl * all + team + tile;
     st_agent((unsigned long long*)p, PS_EMPTY);
   }
-  if (!ps_handshake(pa)) {
-    if (tile == 0 && t0_ == 0 && S->off == 0) S->off = PS_OFF;   // (not over a lost wait)
-    return;
-  }
-  if (idle) return;
+  if (!ps_handshake(pa) || idle) return;
+  ps_stall(pa, tile);
 
   const int64_t N = a.op.N;
   const int64_t base = (int64_t)tile * R;
@@ -493,7 +489,7 @@ k_persist(IterArgs<V, M> a, PersistArgs pa) {
     const int lo = (int)(base - h < 0 ? 0 : (base - h) / R);
     const int hi = (int)min((int64_t)pa.nt - 1, (base + rows - 1 + h) / R);
     bool f = true;
-    for (int q = lo + t; q <= hi; q += PS_TB) f = ps_wait_ge(flag + q, step, bound) && f;
+    for (int q = lo + t; q <= hi; q += PS_TB) f = ps_wait_ge(flag + q, step, lost) && f;
     if (!f) s_bad[0] = 1;
     __syncthreads();
     ok = !s_bad[0];
@@ -619,7 +615,7 @@ k_persist(IterArgs<V, M> a, PersistArgs pa) {
       st_agent(pws + tile, b);
     }
     ok = true;
-    s = ps_wave_sum(ps_gather<1>(pws, pa.nt, bound, ok));
+    s = ps_wave_sum(ps_gather<1>(pws, pa.nt, lost, ok));
     if (lane == 0) redp[1][wid] = s;
     if (!ok) s_bad[1] = 1;
     __syncthreads();
@@ -695,7 +691,7 @@ k_persist(IterArgs<V, M> a, PersistArgs pa) {
         for (int q = 0; q < PS_NW; ++q) b += red[q][v - 2 * KP];
       st_agent(dots + (size_t)tile * NV + v, b);
     }
-    gl[t] = ps_gather<NV>(dots, pa.nt, bound, ok);
+    gl[t] = ps_gather<NV>(dots, pa.nt, lost, ok);
     if (!ok) s_bad[1] = 1;
     __syncthreads();
     if (s_bad[1]) { ok = false; break; }
@@ -776,8 +772,6 @@ k_persist(IterArgs<V, M> a, PersistArgs pa) {
       if (outer_done) S->outer_done = 1;
     }
   }
-  // whichever block gave up: its rows may be an iteration behind the others'
-  if (!ok && t0_ == 0) S->off = PS_LOST;
 }
 
 }  // namespace adef2

@@ -49,7 +49,7 @@ struct PersistTmArgs {
   int64_t gs;           // stride of a group in P, T, Q, X, D
   unsigned* shake;
   unsigned seq, base, nblk;
-  long long shake_ticks, wait_ticks;
+  long long stall;
   int nt, ng;           // tiles, groups
   const int* ids;       // the instances of this launch (those still iterating), nb of them
   int nb;
@@ -61,19 +61,19 @@ struct PersistTmArgs {
 // The handshake takes the words of PersistArgs.
 __device__ __forceinline__ PersistArgs pt_shake_args(const PersistTmArgs& a) {
   PersistArgs p{};
-  p.shake = a.shake; p.seq = a.seq; p.base = a.base; p.nblk = a.nblk;
-  p.shake_ticks = a.shake_ticks;
+  p.shake = a.shake; p.seq = a.seq; p.base = a.base; p.nblk = a.nblk; p.stall = a.stall;
   return p;
 }
 
 // Value at p once it has arrived (bounded; ok becomes false past the bound).
-__device__ __forceinline__ double pt_take(const double* p, const PsBound& bound, bool& ok) {
+__device__ __forceinline__ double pt_take(const double* p, unsigned* lost, bool& ok) {
   unsigned long long b = ps_bits(p);
   if (b == PS_EMPTY) {
     const long long c0 = wall_clock64();
     int n = 0;
     while ((b = ps_bits(p)) == PS_EMPTY) {
-      if ((++n & 63) == 0 && bound.lost(c0)) {
+      if ((++n & 63) == 0 && (ld_agent(lost) != 0u || wall_clock64() - c0 > PS_WAIT_TICKS)) {
+        st_agent(lost, 1u);
         ok = false;
         break;
       }
@@ -149,7 +149,7 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
   const int G = min(PT_G, pa.nb - g0);
   const int* ids = pa.ids + g0;              // the group's instances
   unsigned* flag = pa.flags + (size_t)grp * pa.nt;
-  const PsBound bound{pa.shake + PS_HALT, pa.seq, pa.wait_ticks};
+  unsigned* lost = pa.shake + PS_LOST;
   const size_t allpw = (size_t)pa.ng * pa.nt * PT_G, alld = (size_t)pa.nb * pa.nt * NV, allp = (size_t)pa.ng * PT_G * NP;
   // the instances this block leads, spread over the tiles
   unsigned lead = 0u;
@@ -196,10 +196,8 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
           st_agent((unsigned long long*)(pa.pub + slot * allp + ((size_t)grp * PT_G + i) * NP + v), PS_EMPTY);
   };
   for (int sl = 0; sl < 3; ++sl) clear(t0_, sl);
-  if (!ps_handshake(pt_shake_args(pa))) {
-    if (tile == 0 && t0_ < G && a.inst[ids[t0_]].off == 0) a.inst[ids[t0_]].off = PS_OFF;
-    return;
-  }
+  if (!ps_handshake(pt_shake_args(pa))) return;
+  ps_stall(pt_shake_args(pa), tile);
   const int64_t N = a.op.N;
   const int64_t base = (int64_t)tile * pa.rows;
   const int rows = (int)(N - base < pa.rows ? N - base : pa.rows);
@@ -307,7 +305,7 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
     const int lo = (int)(base - h < 0 ? 0 : (base - h) / pa.rows);
     const int hi = (int)min((int64_t)pa.nt - 1, (base + rows - 1 + h) / pa.rows);
     bool f = true;
-    for (int q = lo + t; q <= hi; q += PT_TB) f = ps_wait_ge(flag + q, step, bound) && f;
+    for (int q = lo + t; q <= hi; q += PT_TB) f = ps_wait_ge(flag + q, step, lost) && f;
     if (!f) s_bad = 1;
     __syncthreads();
     ok = !s_bad;
@@ -530,7 +528,10 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
             for (int u = 0; u < 8; ++u) wait |= b[u] == PS_EMPTY;
             if (wait && (++n & 63) == 0) {
               if (n == 64) c0 = wall_clock64();
-              if (bound.lost(c0)) ok = wait = false;
+              if (ld_agent(lost) != 0u || wall_clock64() - c0 > PS_WAIT_TICKS) {
+                st_agent(lost, 1u);
+                ok = wait = false;
+              }
             }
           }
 #pragma unroll
@@ -744,7 +745,10 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
             for (int u = 0; u < U; ++u) wait |= b[u] == PS_EMPTY;
             if (wait && (++n & 63) == 0) {
               if (n == 64) c0 = wall_clock64();
-              if (bound.lost(c0)) ok = wait = false;
+              if (ld_agent(lost) != 0u || wall_clock64() - c0 > PS_WAIT_TICKS) {
+                st_agent(lost, 1u);
+                ok = wait = false;
+              }
             }
           }
 #pragma unroll
@@ -812,7 +816,7 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
       for (int e = t; e < G * NP; e += PT_TB) {
         const int li = e / NP, v = e - li * NP;
         if (!s_live[li]) continue;
-        const double b = pt_take(pub + e, bound, ok);
+        const double b = pt_take(pub + e, lost, ok);
         if (v < KP) cfs[li][v] = b;
         else if (v == KP) s_beta[li] = b;
         else if (v == KP + 1) s_rho[li] = b;
@@ -858,7 +862,6 @@ __global__ void __launch_bounds__(PT_TB) k_persist_tm(IterArgs<double, float> a,
       if (s_done[i] == 2) S->outer_done = 1;
     }
   }
-  if (!ok && t0_ < G) a.inst[ids[t0_]].off = PS_LOST;
 }
 
 }  // namespace adef2

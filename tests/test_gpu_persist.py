@@ -213,9 +213,9 @@ def test_breakdown_stays_in_its_instance(lib):
 # 16 tiles an instance; groups of 16, listed rows through LDS; FP32 vectors
 @pytest.mark.parametrize("prec,n,k,B,form", [("fp64", 63, 16, 2, 1), ("mixed", 91, 8, 57, 2), ("fp32", 63, 8, 3, 1)])
 def test_a_wait_that_is_given_up_costs_time_only(lib, prec, n, k, B, form):
-    """Blocks that give up their first wait (bound 0) leave instances with vectors
-    of different iterations: the solve starts again with a kernel per step, whatever
-    the launches queued behind did, and the next solve runs chunk launches again."""
+    """Blocks that give up a wait (for a block that starts 1 ms late) leave instances
+    with vectors of different iterations: the solve starts again with a kernel per
+    step, and the next one runs chunk launches again."""
     w = gen.c2_workload(n=n, k=k, B=B)
     masks = np.stack([i.mask for i in w.instances])
     bs = np.stack([i.b for i in w.instances])
@@ -224,22 +224,19 @@ def test_a_wait_that_is_given_up_costs_time_only(lib, prec, n, k, B, form):
                precision=dict(fp64=lib.FP64, mixed=lib.MIXED_REFINE, fp32=lib.FP32_REFINE)[prec])
     tol = 1e-8
     S = spec(w.op, "factored")
-    for bound, from_launch in ((0, 0), (0, 3), (-1, 0)):
-        s.set_chunk_bounds(wait_us=bound, from_launch=from_launch)
-        lost = s.chunk_variant()["lost"] if from_launch or bound else 0
+    for fault, from_launch, lost in ((2, 0, 1), (2, 3, 2), (0, 0, 2)):
+        s.chunk_fault(fault, from_launch)
         out = s.solve_batched(masks, bs, tol)
         v = s.chunk_variant()
-        print(f"   bound {bound} from launch {from_launch}: {v}", flush=True)
-        if bound == 0:
-            assert v["lost"] == lost + 1 and v["launches"] == 0 and v["form"] == 0
-        else:
-            assert v["lost"] == lost and v["launches"] > 0 and v["form"] == form
+        print(f"   fault {fault} from launch {from_launch}: {v}", flush=True)
+        assert v["lost"] == lost and v["called_off"] == 0
+        assert v["form"] == (0 if fault else form) and (v["launches"] == 0) == (fault != 0)
         _check(lib, w, S, out, prec, (0, B - 1), tol)
 
 
 @pytest.mark.parametrize("prec,n,k,B", [("fp64", 63, 16, 2), ("mixed", 91, 8, 57), ("fp32", 63, 8, 3)])
 def test_called_off_launches_step_back(lib, prec, n, k, B):
-    """A chunk launch that is called off (bound 0) leaves its solve to the kernels per
+    """A chunk launch that is called off leaves its solve to the kernels per
     step: the tuned ones when it is the first launch, from where the solve is when it
     is a later one. The next solves remember it."""
     w = gen.c2_workload(n=n, k=k, B=B)
@@ -252,7 +249,7 @@ def test_called_off_launches_step_back(lib, prec, n, k, B):
     for from_launch in (0, 3):
         s = solver(lib, w.op, w.Z, "factored", profile=1,
                    precision=dict(fp64=lib.FP64, mixed=lib.MIXED_REFINE, fp32=lib.FP32_REFINE)[prec])
-        s.set_chunk_bounds(handshake_us=0, from_launch=from_launch)
+        s.chunk_fault(1, from_launch)
         out = s.solve_batched(masks, bs, tol)
         v, st = s.chunk_variant(), s.stats()
         print(f"   from launch {from_launch}: {v}, trial ms {s.variant()[2].max():.2f}", flush=True)
@@ -268,7 +265,7 @@ def test_called_off_launches_step_back(lib, prec, n, k, B):
             tries.append(s.chunk_variant()["called_off"])
         if from_launch == 0:
             assert tries == [1, 1, 2, 2, 2, 2, 2], tries
-        s.set_chunk_bounds()
+        s.chunk_fault(0)
         out = s.solve_batched(masks, bs, tol)
         assert s.chunk_variant()["form"] > 0
         _check(lib, w, S, out, prec, (0, B - 1), tol)
@@ -283,7 +280,7 @@ def test_called_off_launches_and_the_iteration_cap(lib, from_launch):
     bs = np.stack([i.b for i in w.instances])
     case(f"called off at launch {from_launch}, then the iteration cap")
     s = solver(lib, w.op, w.Z, "factored", precision=lib.MIXED_REFINE, maxit=150, segment_maxit=5)
-    s.set_chunk_bounds(handshake_us=0, from_launch=from_launch)
+    s.chunk_fault(1, from_launch)
     out = s.solve_batched(masks, bs, 1e-10)
     v = s.chunk_variant()
     print(f"   {v} iters {out['iters']}", flush=True)
