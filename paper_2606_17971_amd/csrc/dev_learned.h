@@ -198,8 +198,9 @@ __global__ void __launch_bounds__(JTB) k_jacobi_rot(int n, const double* A, doub
     off = dia = 0.0;
     for (int w = 0; w < JTB / 64; ++w) { off += red[0][w]; dia += red[1][w]; }
     // diagonal, or at rounding level and no longer shrinking (the null space of
-    // a rank-deficient Gram)
-    if (!(off > 1e-30 * dia) || (off <= 1e-27 * dia && off > 0.25 * prev)) break;
+    // a rank-deficient Gram; eigenvalues 1e-14 of the largest are still being
+    // separated at this level, by a factor of 3 to 10 a sweep)
+    if (!(off > 1e-30 * dia) || (off <= 1e-27 * dia && off > 0.9 * prev)) break;
     prev = off;
     for (int rnd = 0; rnd < g.rounds; ++rnd, ++done) {
       if (tid < np) {

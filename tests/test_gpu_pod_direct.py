@@ -35,3 +35,22 @@ def test_direct_pod_matches_numpy(lib, M, p):
     off = 1.0 - np.abs(np.sum(Phi * Ux[:, :p], axis=0))
     assert np.all(off <= (10 * M * eps * lam[0] / gap) ** 2 + 100 * eps * lam[0] / lam[:p])
     assert np.abs(Phi.T @ Phi - np.eye(p)).max() <= 10 * M * eps * lam[0] / lam[p - 1]
+
+
+def test_direct_pod_separates_small_modes(lib):
+    """Snapshots that hardly differ: one mode and 99 of 1e-7 to 2e-7 of its size.  The
+    modes stay orthonormal as far as the Gram's rounding allows: entries of
+    eps / M, a matrix of norm 2 eps / sqrt(M), twice for the sums behind them and
+    once more for the eigensolver, over lambda_j >= tail^2 (in units of lambda_1)."""
+    M, p, tail = 100, 16, 2e-7
+    w = gen.c1_workload(n=31, k=0)
+    rng = np.random.default_rng(M)
+    U = np.linalg.qr(rng.standard_normal((w.op.N, M)))[0]
+    V = np.linalg.qr(rng.standard_normal((M, M)))[0]
+    X = (U * np.r_[1.0, tail * np.linspace(1.0, 0.5, M - 1)]) @ V.T
+    case("direct pod, small modes")
+    s = solver(lib, w.op, None, "assembled")
+    Phi = s.pod(np.asfortranarray(X), p)[0].cpu().numpy()
+    orth = np.abs(Phi.T @ Phi - np.eye(p)).max()
+    print(f"   orthonormal to {orth:.2e}", flush=True)
+    assert orth <= 5 * np.finfo(np.float64).eps / M ** 0.5 / tail ** 2
