@@ -587,19 +587,21 @@ int adef2_update_variant(adef2_ctx *ctx, int32_t *warp_specialised, int32_t *til
  * it changes anything, and the solve goes on with a kernel per step (the tuned
  * ones, if it was the first launch or an earlier solve has tuned them).  When a
  * block has waited 4 s for another one, it gives the launch up, and the solve
- * starts again with a kernel per step.  After either the context's next 2 solves
- * make no chunk launches, then one tries again (4 the next time, up to 64, until
- * one goes through).  called_off, lost: solves of this context to which the one
- * and the other happened.  Any pointer may be NULL.  E_STATE before the first
+ * starts again with a kernel per step.  It runs a kernel per step too when there is
+ * no memory for the buffers that the blocks exchange data in.  After any of these
+ * the context's next 2 solves make no chunk launches, then one tries again (4 the
+ * next time, up to 64, until one goes through).  called_off, lost: solves of this context to which the first
+ * and the second happened.  Any pointer may be NULL.  E_STATE before the first
  * solve. */
 int adef2_chunk_variant(adef2_ctx *ctx, int32_t *form, int32_t *rows, int64_t *launches, int64_t *called_off,
                         int64_t *lost);
 
-/* For tests: what goes wrong with the chunk launches of the next solves, from
- * launch from_launch (>= 0) of a solve on.  kind 1: they are called off; 2: blocks
- * start 1 ms late and those that wait for them give up; 0: nothing.  Also forgets
- * earlier call-offs (see adef2_chunk_variant). */
-int adef2_chunk_fault(adef2_ctx *ctx, int32_t kind, int32_t from_launch);
+/* For tests: what goes wrong in the next calls.  kind 1: chunk launches are called
+ * off, from launch at (>= 0) of a solve on; 2: from that launch on blocks start 1 ms
+ * late and those that wait for them give up; 3: device allocation number at (from
+ * 0) from now on fails, once; 0: nothing.  Also forgets earlier call-offs (see
+ * adef2_chunk_variant). */
+int adef2_fault(adef2_ctx *ctx, int32_t kind, int32_t at);
 
 #define ADEF2_STATS_KERNELS 24
 typedef struct {

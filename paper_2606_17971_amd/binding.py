@@ -104,7 +104,7 @@ _sig = {
     "adef2_operator_variant": (ctypes.c_int, [_P, _Pi32, _Pi32, _Pi32, _P]),
     "adef2_update_variant": (ctypes.c_int, [_P, _Pi32, _Pi32, _P]),
     "adef2_chunk_variant": (ctypes.c_int, [_P, _Pi32, _Pi32, _Pi64, _Pi64, _Pi64]),
-    "adef2_chunk_fault": (ctypes.c_int, [_P, _i32, _i32]),
+    "adef2_fault": (ctypes.c_int, [_P, _i32, _i32]),
     "adef2_active_set_batched": (ctypes.c_int, [_P, _i32, _P, _P, _f64, _f64, _i32, _P, _P, _P, _P, _P]),
     "adef2_pod_enrich": (ctypes.c_int, [_P, _i32, _f64]),
     "adef2_set_enrichment": (ctypes.c_int, [_P, _i32, _P, _P, _i32, _f64]),
@@ -458,9 +458,10 @@ class Solver:
                                              ctypes.byref(off), ctypes.byref(lost)), allow=(OK,))
         return dict(form=f.value, rows=r.value, launches=n.value, called_off=off.value, lost=lost.value)
 
-    def chunk_fault(self, kind=0, from_launch=0):
-        """Tests: chunk launches called off (1), waits given up (2), neither (0)."""
-        self._check(_lib.adef2_chunk_fault(self._ctx, int(kind), int(from_launch)), allow=(OK,))
+    def fault(self, kind=0, at=0):
+        """Tests: chunk launches called off (1) or waits given up (2) from launch
+        `at` of a solve on, device allocation `at` from now fails (3), none (0)."""
+        self._check(_lib.adef2_fault(self._ctx, int(kind), int(at)), allow=(OK,))
 
     def op_variant(self):
         """(fused, tile rows, trial ms [two passes, fused at 2 / 4 / 8 x the

@@ -241,6 +241,7 @@ struct adef2_ctx {
   unsigned ps_seq = 0, ps_base = 0;
   bool ps_ready = false;         // handshake words cleared for this sequence of launches
   int ps_fault = 0, ps_from = 0; // tests: what goes wrong, from which launch of a solve on
+  int alloc_fault = -1;          // tests: allocations until one fails (-1: none does)
   bool no_chunk = false;         // this solve (or what is left of it) runs without chunk launches
   // after a solve that stepped back: solves to leave without chunk launches, and
   // how many that were the last time (0: the last chunk launches went through)
@@ -293,9 +294,11 @@ template <typename T>
 int dalloc(adef2_ctx* c, T** p, size_t count) {
   if (*p) { hipFree(*p); *p = nullptr; }
   if (count == 0) return ADEF2_OK;
-  hipError_t e = hipMalloc((void**)p, count * sizeof(T));
+  hipError_t e = c->alloc_fault >= 0 && c->alloc_fault-- == 0 ? hipErrorOutOfMemory
+                                                              : hipMalloc((void**)p, count * sizeof(T));
   if (e != hipSuccess) {
     *p = nullptr;
+    hipGetLastError();                 // (a later launch is not to report it)
     return fail(c, ADEF2_E_NOMEM, std::string("hipMalloc of ") + std::to_string(count * sizeof(T)) +
                                       " bytes failed: " + hipGetErrorString(e));
   }
@@ -581,7 +584,7 @@ int ensure_batch(adef2_ctx* c, int B, int prec) {
   c->B = B;
   if (same) return ADEF2_OK;
   int rc;
-  c->Bcap = B;
+  c->Bcap = 0;                       // until every buffer is there
   c->KPalloc = KP;
   c->prec = prec;
   c->vs = N + 2 * c->H;
@@ -645,6 +648,7 @@ int ensure_batch(adef2_ctx* c, int B, int prec) {
   if ((rc = dalloc(c, &c->part, c->part_elems))) return rc;
   if ((rc = dalloc(c, &c->ctr, c->ctr_elems))) return rc;
   HIPCHK(c, hipMemsetAsync(c->ctr, 0, c->ctr_elems * sizeof(unsigned), c->st));
+  c->Bcap = B;
   return ADEF2_OK;
 }
 
@@ -1334,6 +1338,17 @@ void persist_step_back(adef2_ctx* c) {
   c->ps_skip = c->ps_back;
 }
 
+// Gives the exchange buffers back.
+void persist_free(adef2_ctx* c) {
+  for (double** q : {&c->ps_pw, &c->ps_dots, &c->pt_P, &c->pt_T, &c->pt_Q, &c->pt_X, &c->pt_D, &c->pt_pw, &c->pt_dots,
+                     &c->pt_pub})
+    if (*q) { hipFree(*q); *q = nullptr; }
+  for (unsigned** q : {&c->ps_flags, &c->pt_flags})
+    if (*q) { hipFree(*q); *q = nullptr; }
+  c->ps_tiles = c->ps_vals = c->pt_tiles = c->pt_vals = c->pt_pubs = 0;
+  c->pt_N = 0;
+}
+
 // Takes the instances that still iterate (all: every one) as the list of the
 // persistent kernels' next launches and plans for them; persist: whether one
 // applies.  The stream is idle when the list changes.
@@ -1348,14 +1363,24 @@ int persist_live(adef2_ctx* c, bool all, bool outer, bool* persist) {
   c->nlive = (int)ids.size();
   *persist = c->nlive > 0 && persist_plan(c);
   if (!*persist) return ADEF2_OK;
-  int rc;
+  // the kernels per step need no buffers of their own: without room for these the
+  // solve goes on with them
+  int rc = ADEF2_OK;
   if ((size_t)c->B > c->live_cap) {
     c->live_cap = 0;
-    if ((rc = dalloc(c, &c->live_d, (size_t)c->B))) return rc;
-    c->live_cap = c->B;
+    rc = dalloc(c, &c->live_d, (size_t)c->B);
+    if (!rc) c->live_cap = c->B;
   }
+  if (!rc) rc = c->pt_e ? persist_tm_buffers(c) : persist_buffers(c);
+  if (rc == ADEF2_E_NOMEM) {
+    persist_free(c);
+    persist_step_back(c);
+    *persist = false;
+    return ADEF2_OK;
+  }
+  if (rc) return rc;
   HIPCHK(c, hipMemcpyAsync(c->live_d, c->live_h.data(), sizeof(int) * c->nlive, hipMemcpyHostToDevice, c->st));
-  return c->pt_e ? persist_tm_buffers(c) : persist_buffers(c);
+  return ADEF2_OK;
 }
 
 // max_chunks > 0 stops after that many chunks (tuning trials).
@@ -1435,6 +1460,7 @@ int run_sweep(adef2_ctx* c, const double* src, const double* x0pad, double thres
   if (may_persist) {
     int rc = persist_live(c, true, b_outer != nullptr, &persist);
     if (rc) return rc;
+    if (c->no_chunk) return RC_REDO;           // (no room for its buffers)
   }
   auto launch_chunk = [&](hipStream_t s) {
     if (persist)
@@ -1564,6 +1590,7 @@ int run_sweep(adef2_ctx* c, const double* src, const double* x0pad, double thres
     if (ad) break;
     // fewer instances may fit where all did not, or need fewer tiles or groups
     if (may_persist && (rc = persist_live(c, false, b_outer != nullptr, &persist))) return rc;
+    may_persist = may_persist && !c->no_chunk;
     if (!persist && !gexec && (grc = make_graph())) return grc;
     // every instance stops at maxit on the device; this guards the host loop
     if (launched > (int64_t)c->o.maxit + (int64_t)(pmax + 2) * chunk)
@@ -2717,12 +2744,13 @@ int adef2_variant(adef2_ctx* c, int32_t* rows_per_thread, int32_t* w_mode, float
   return ADEF2_OK;
 }
 
-int adef2_chunk_fault(adef2_ctx* c, int32_t kind, int32_t from_launch) {
+int adef2_fault(adef2_ctx* c, int32_t kind, int32_t at) {
   if (!c) return ADEF2_E_ARG;
-  if (kind < 0 || kind > 2 || from_launch < 0) return fail(c, ADEF2_E_ARG, "chunk fault 0, 1 or 2, from_launch >= 0");
-  c->ps_fault = kind;
-  c->ps_from = from_launch;
+  if (kind < 0 || kind > 3 || at < 0) return fail(c, ADEF2_E_ARG, "fault 0, 1, 2 or 3, at >= 0");
+  c->ps_fault = kind < 3 ? kind : 0;
+  c->ps_from = at;
   c->ps_skip = c->ps_back = 0;
+  c->alloc_fault = kind == 3 ? at : -1;
   return ADEF2_OK;
 }
 

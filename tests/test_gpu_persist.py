@@ -225,7 +225,7 @@ def test_a_wait_that_is_given_up_costs_time_only(lib, prec, n, k, B, form):
     tol = 1e-8
     S = spec(w.op, "factored")
     for fault, from_launch, lost in ((2, 0, 1), (2, 3, 2), (0, 0, 2)):
-        s.chunk_fault(fault, from_launch)
+        s.fault(fault, from_launch)
         out = s.solve_batched(masks, bs, tol)
         v = s.chunk_variant()
         print(f"   fault {fault} from launch {from_launch}: {v}", flush=True)
@@ -249,7 +249,7 @@ def test_called_off_launches_step_back(lib, prec, n, k, B):
     for from_launch in (0, 3):
         s = solver(lib, w.op, w.Z, "factored", profile=1,
                    precision=dict(fp64=lib.FP64, mixed=lib.MIXED_REFINE, fp32=lib.FP32_REFINE)[prec])
-        s.chunk_fault(1, from_launch)
+        s.fault(1, from_launch)
         out = s.solve_batched(masks, bs, tol)
         v, st = s.chunk_variant(), s.stats()
         print(f"   from launch {from_launch}: {v}, trial ms {s.variant()[2].max():.2f}", flush=True)
@@ -265,7 +265,7 @@ def test_called_off_launches_step_back(lib, prec, n, k, B):
             tries.append(s.chunk_variant()["called_off"])
         if from_launch == 0:
             assert tries == [1, 1, 2, 2, 2, 2, 2], tries
-        s.chunk_fault(0)
+        s.fault(0)
         out = s.solve_batched(masks, bs, tol)
         assert s.chunk_variant()["form"] > 0
         _check(lib, w, S, out, prec, (0, B - 1), tol)
@@ -280,9 +280,47 @@ def test_called_off_launches_and_the_iteration_cap(lib, from_launch):
     bs = np.stack([i.b for i in w.instances])
     case(f"called off at launch {from_launch}, then the iteration cap")
     s = solver(lib, w.op, w.Z, "factored", precision=lib.MIXED_REFINE, maxit=150, segment_maxit=5)
-    s.chunk_fault(1, from_launch)
+    s.fault(1, from_launch)
     out = s.solve_batched(masks, bs, 1e-10)
     v = s.chunk_variant()
     print(f"   {v} iters {out['iters']}", flush=True)
     assert v["called_off"] == 1
     assert np.all(out["status"] == lib.W_MAXIT) and np.all(out["iters"] == 150)
+
+
+@pytest.mark.parametrize("prec,n,k,B,form", [("fp64", 31, 8, 2, 1), ("mixed", 91, 8, 57, 2)])
+def test_allocations_that_fail(lib, prec, n, k, B, form):
+    """Each allocation of a first solve fails in turn.  The chunk launches' buffers
+    are not needed to solve: without them the kernels per step run. After any other
+    the solve says E_NOMEM, and the next one finds everything it needs."""
+    w = gen.c2_workload(n=n, k=k, B=B)
+    masks = np.stack([i.mask for i in w.instances])
+    bs = np.stack([i.b for i in w.instances])
+    S = spec(w.op, "factored")
+    tol = 1e-8
+    solved = refused = 0
+    s = solver(lib, w.op, w.Z, "factored", precision=dict(fp64=lib.FP64, mixed=lib.MIXED_REFINE)[prec])
+    ref = s.solve_batched(masks, bs, tol)
+    _check(lib, w, S, ref, prec, (0, B - 1), tol)
+    ref = ref["x"].cpu().numpy()
+    for at in range(100):
+        case(f"allocation {at} fails, {prec} cd2d n={n} B={B}")
+        s = solver(lib, w.op, w.Z, "factored", precision=dict(fp64=lib.FP64, mixed=lib.MIXED_REFINE)[prec])
+        s.fault(3, at)
+        try:
+            x = s.solve_batched(masks, bs, tol)["x"].cpu().numpy()
+            first = s.chunk_variant()["form"]
+            assert np.linalg.norm(x - ref) <= 1e-6 * np.linalg.norm(ref)
+            solved += first == 0
+        except lib.Adef2Error as e:
+            assert e.code == lib.E_NOMEM
+            refused += 1
+            first = 0
+        s.fault()
+        x = s.solve_batched(masks, bs, tol)["x"].cpu().numpy()
+        assert s.chunk_variant()["form"] == form
+        assert np.linalg.norm(x - ref) <= 1e-6 * np.linalg.norm(ref)
+        if first == form:                          # fewer allocations than that
+            break
+    print(f"   {solved} solved without chunk launches, {refused} refused", flush=True)
+    assert first == form and solved >= 4 and refused >= 20
