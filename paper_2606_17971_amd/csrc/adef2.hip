@@ -3065,7 +3065,8 @@ int adef2_learned_set_params(adef2_ctx* c, const float* params, double tau_learn
   if (!c || !params) return ADEF2_E_ARG;
   if (!(tau_learned >= 1.0)) return fail(c, ADEF2_E_ARG, "tau_learned must be >= 1");
   int rc;
-  if (!c->mlp) {
+  if (!c->mlp_part) {                // (the last of them)
+    c->have_mlp = false;
     if ((rc = dalloc(c, &c->mlp, NPARAM)) || (rc = dalloc(c, &c->mlp_bf, NPARAM)) ||
         (rc = dalloc(c, &c->mlp_g, NPARAM)) || (rc = dalloc(c, &c->mlp_m, NPARAM)) ||
         (rc = dalloc(c, &c->mlp_v, NPARAM)) || (rc = dalloc(c, &c->mlp_part, (size_t)WG_SLICES * NPARAM)))

@@ -30,3 +30,27 @@ def test_gradient_of_repeated_samples(lib, setup, distinct, M):
     np.testing.assert_allclose(l1, np.tile(l0, M // distinct), rtol=1e-12)
     for a, b in ((0, 512), (512, 640), (640, 17024), (17024, 17152), (17152, 82688), (82688, g0.size)):
         assert np.linalg.norm(g1[a:b].astype(float) - g0[a:b]) <= 1e-4 * np.linalg.norm(g0[a:b].astype(float)), (a, b)
+
+
+@pytest.mark.parametrize("at", range(6))
+def test_parameters_after_an_allocation_failed(lib, setup, at):
+    """Setting the parameters again after one of their buffers had no room finds all
+    of them: the gradient is that of a context with room."""
+    w, op, thetas, insts, xs, X, Phi, sig = setup
+    print(f"[case] network parameters after allocation {at} failed", flush=True)
+    _, flat = _params(3)
+    got = []
+    for fails in (False, True):
+        s = lib.Solver()
+        s.set_reference_factored(op.A, op.alpha, op.shift, w.Z)
+        s.set_pod_modes(Phi)
+        if fails:
+            s.fault(3, at)
+            with pytest.raises(lib.Adef2Error) as e:
+                s.learned_set_params(flat)
+            assert e.value.code == lib.E_NOMEM
+        s.learned_set_params(flat)
+        s.learned_prepare(np.stack([insts[m].mask for m in range(4)]), np.stack([insts[m].b for m in range(4)]),
+                          xs[:4], thetas[:4].astype(np.float32))
+        got.append(s.learned_loss_grad())
+    np.testing.assert_array_equal(got[0][1], got[1][1])
