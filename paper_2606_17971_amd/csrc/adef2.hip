@@ -870,13 +870,14 @@ IterArgs<V, M> iter_args(adef2_ctx* c) {
 // algorithmic bytes per launch (per instance: inactive rows only); wv / wm =
 // bytes per vector entry / per operator or panel entry
 struct ByteModel { double init, init2, pupdate, stencil, spmv, update, resid, accum, update_nw, zproj, update_tm,
-                   finish_tm, opfused; };
+                   finish_tm, opfused, chunk_it, chunk; };
 // Algorithmic bytes per launch.  Per-instance data (vectors, W, the mask) is
 // counted for every instance still iterating at the last poll (a finished
 // instance's blocks exit at their first instruction); operands shared by
 // all instances (Z, the stencil coefficients) are counted once per launch,
 // over min(N, total inactive rows) rows for Z and the outer stencil and N
 // rows for the inner stencil of the factored operator.
+int persist_form(const adef2_ctx* c);
 ByteModel byte_model(const adef2_ctx* c, double wv, double wm, bool sweep_active = true) {
   const double k = c->KP > 0 ? (double)c->k : 0.0;
   double nI = 0.0;
@@ -913,6 +914,15 @@ ByteModel byte_model(const adef2_ctx* c, double wv, double wm, bool sweep_active
   // tile partial sums of the iterating instances, the slice totals written and read back
   const double nv = 2.0 * (double)c->KP + 2.0;
   b.finish_tm = (double)nact * nv * 8.0 * ((double)fin_leaves(c) + 2.0 * fin_slices(fin_leaves(c)));
+  // chunk launches: an iteration reads the operator, the modes for Z c and for the
+  // products, and W (whole, on the boundary rows, or the operator again in its
+  // place); p goes through memory for the neighbouring tiles.  The other vectors
+  // are read and written once per launch
+  const bool bform = c->ne > 0, wfree = !bform && c->KP > 0 && mat64(c->prec) && persist_form(c) == PS_FREE;
+  const double op = U * D * wm + (c->factored ? N1 * D1 * wm : 0.0);
+  b.chunk_it = op + Nall * wv + nI * wv + 2.0 * zsh +
+               (bform ? (double)c->nbnd * (4.0 + k * wm) : wfree ? op + Nall * wv + nI * wv : nI * k * wm);
+  b.chunk = nI * 9 * wv + Nall;                                // x r z p dinv -> x r z p
   // (t = A z), z, r; Z^T u, Z^T r with the FP64 operator and modes
   const double inner64 = c->factored ? (Nall * 2 * wv + N1 * D1 * 8.0) : 0.0;
   b.zproj = inner64 + nI * 3 * wv + U * D * 8.0 + zsh * (8.0 / wm) + Nall;
@@ -1464,7 +1474,7 @@ int run_sweep(adef2_ctx* c, const double* src, const double* x0pad, double thres
   }
   auto launch_chunk = [&](hipStream_t s) {
     if (persist)
-      timed(c, KI_CHUNK, chunk * (bm.pupdate + bm.stencil + bm.spmv + bm.update),
+      timed(c, KI_CHUNK, chunk * bm.chunk_it + bm.chunk,
             [&] {
               if constexpr (sizeof(V) == 8 && sizeof(M) == 4)
                 if (c->pt_e) return launch_persist_tm(c, a, chunk, s);

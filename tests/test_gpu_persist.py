@@ -324,3 +324,23 @@ def test_allocations_that_fail(lib, prec, n, k, B, form):
             break
     print(f"   {solved} solved without chunk launches, {refused} refused", flush=True)
     assert first == form and solved >= 4 and refused >= 20
+
+
+def test_chunk_launch_bytes(lib):
+    """The bytes of a chunk launch in stats(): 32 iterations read the operator and
+    move p, everything else moves once."""
+    w = gen.c2_workload(n=63, k=16, B=1)
+    mask, b = w.instances[0].mask, w.instances[0].b
+    N, nI = mask.size, int((mask == 0).sum())
+    case("chunk launch bytes, fp64 63^2, k = 0 and 16")
+
+    def diagonals(A):
+        return np.unique(A.indices - np.repeat(np.arange(N), np.diff(A.indptr))).size
+
+    D, D1 = diagonals(w.op.S()), diagonals(w.op.A)
+    for form, k, op in (("assembled", 0, nI * D * 8), ("factored", 16, (N * D1 + nI * D1) * 8)):
+        s = solver(lib, w.op, w.Z if k else None, form, profile=1, poll_max=1)
+        s.solve_batched(mask[None], b[None], 1e-6)
+        st = s.stats()["chunk"]
+        it = op + N * 8 + nI * 8 + 3 * nI * k * 8          # p read and written; Z twice, W
+        assert st["alg_bytes"] / st["launches"] == 32 * it + nI * 9 * 8 + N
