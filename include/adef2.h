@@ -172,7 +172,14 @@ typedef struct {
                            the fastest per context (batch size, precision,
                            basis width, operator form, N) and reuses it, so
                            repeated solves in one context are bitwise
-                           reproducible                                     */
+                           reproducible, unless chunk launches step back
+                           (adef2_chunk_variant).  Chunk launches are planned
+                           for the instances that iterate at a poll; where
+                           they run, another poll_max, another sweep_async or
+                           other instances in the batch change the order of
+                           sums.  With any of the options named at
+                           check_every set, no chunk launch is made and an
+                           instance's arithmetic depends on none of these   */
   int32_t w_boundary;   /* 1: with FP32 panels, reference modes that are
                            eigenvectors of the reference operator B
                            (||B z - mu z|| <= 1e-6 |mu| ||z||, tested at
@@ -269,7 +276,8 @@ typedef struct {
                            segments; 0 = every instance's segment must end
                            before the host starts the next segment for all.
                            The arithmetic of every instance is the same
-                           either way (same iterations, same x)             */
+                           either way (same iterations, same x) unless chunk
+                           launches run (see w_mode)                        */
   int32_t update_ws;    /* update kernel of the tile-major boundary-form path
                            (w_mode 4 and 5, at most 32 modes): 1 = warp-
                            specialised, each block of 8 waves owns a run of
@@ -553,14 +561,16 @@ int adef2_active_set_batched(adef2_ctx *ctx, int32_t B, const double *y_d, const
                              uint8_t *masks_out, int32_t *outer, int32_t *inner_iters,
                              int32_t *status);
 
-/* Iteration-kernel variant used by the last solve on ctx: rows per thread
+/* Variant of the kernels per step of the last solve on ctx: rows per thread
  * (1 or 2) and w_mode (1 .. 5 as in adef2_opts), whether fixed by the
- * options or tuned.  ms (host f32[10], may be NULL) receives the trial times
+ * options or tuned.  This query and the two below name what ran when the solve
+ * made no chunk launches or only for its last instances; when it made them from
+ * the start (adef2_chunk_variant), what stood by for them.  ms (host f32[10], may be NULL) receives the trial times
  * of the tuned candidates, rows per thread outer, w_mode inner, restricted to
  * the candidates tried (0 when not tuned).  E_STATE before the first solve. */
 int adef2_variant(adef2_ctx *ctx, int32_t *rows_per_thread, int32_t *w_mode, float *ms);
 
-/* Operator form used by the last solve on ctx (see opts.op_fused): fused
+/* Operator form of the kernels per step (see opts.op_fused): fused
  * (1) or two passes (0), the fused pass's tile height in rows and its
  * instances per block (1, or 4 when the coefficients of a row are shared by
  * a group of instances; both 0 when not fused), and in ms (host f32[7], may
@@ -571,7 +581,7 @@ int adef2_variant(adef2_ctx *ctx, int32_t *rows_per_thread, int32_t *w_mode, flo
  * tuned).  E_STATE before the first solve. */
 int adef2_operator_variant(adef2_ctx *ctx, int32_t *fused, int32_t *tile_rows, int32_t *group, float *ms);
 
-/* Update kernel used by the last solve on ctx (see opts.update_ws):
+/* Update kernel of the kernels per step (see opts.update_ws):
  * warp-specialised (1) or one block per tile (0), the tiles per block (0
  * when the tile-major path is not in use), and in ms (host f32[2], may be
  * NULL) the tuning trial times of the two forms (0 when not tuned).

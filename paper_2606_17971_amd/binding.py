@@ -432,7 +432,8 @@ class Solver:
         return dict(Z=Z.reshape(r, self.n).T, lam=lam, resid=res, iters=it.value, status=rc)
 
     def variant(self):
-        """(rows_per_thread, w_mode, trial ms) of the last solve."""
+        """(rows_per_thread, w_mode, trial ms) of the last solve's kernels per step
+        (what stood by, where chunk_variant() reports chunk launches)."""
         r, wm = _i32(0), _i32(0)
         ms = np.zeros(10, np.float32)
         self._check(_lib.adef2_variant(self._ctx, ctypes.byref(r), ctypes.byref(wm), ms.ctypes.data),

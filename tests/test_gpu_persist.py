@@ -344,3 +344,29 @@ def test_chunk_launch_bytes(lib):
         st = s.stats()["chunk"]
         it = op + N * 8 + nI * 8 + 3 * nI * k * 8          # p read and written; Z twice, W
         assert st["alg_bytes"] / st["launches"] == 32 * it + nI * 9 * 8 + N
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_what_is_bitwise_by_default(lib, prec):
+    """Default options, 60 instances that start with a kernel per step (FP64; tuned)
+    or in groups of 16 (mixed) and end in smaller chunk launches: a repeated solve is
+    bitwise the same. The launches follow the instances left at each poll, so with
+    another poll_max or sweep_async the sums have another order, and the solutions
+    agree to the bars of the parity tests."""
+    w = gen.c2_workload(n=95, k=16, B=60)
+    S = spec(w.op, "factored")
+    masks = np.stack([i.mask for i in w.instances])
+    bs = np.stack([i.b for i in w.instances])
+    tol = 1e-8
+    case(f"repeated solves, polls and segments, {prec} cd2d n=95 B=60")
+    p = dict(fp64=lib.FP64, mixed=lib.MIXED_REFINE)[prec]
+    s = solver(lib, w.op, w.Z, "factored", precision=p)
+    a, b = s.solve_batched(masks, bs, tol), s.solve_batched(masks, bs, tol)
+    np.testing.assert_array_equal(a["iters"], b["iters"])
+    np.testing.assert_array_equal(a["x"].cpu().numpy(), b["x"].cpu().numpy())
+    assert s.chunk_variant()["launches"] > 0
+    if prec == "fp64":
+        assert s.variant()[2].max() > 0                # trial times: the tuner ran
+    for opts in (dict(poll_max=1), dict(sweep_async=0)):
+        s = solver(lib, w.op, w.Z, "factored", precision=p, **opts)
+        _check(lib, w, S, s.solve_batched(masks, bs, tol), prec, (0, 29, 59), tol)
