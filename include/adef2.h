@@ -137,8 +137,9 @@ typedef struct {
                            all 0, and the blocks of the instances that still
                            iterate all resident at once: per instance, or in
                            groups of 16 in the boundary form), else one HIP
-                           graph of check_every iterations of every kernel;
-                           32                                               */
+                           graph of check_every iterations of every kernel.
+                           A solve that starts with chunk launches tunes
+                           nothing; 32                                      */
   int32_t rows_per_thread; /* rows per thread of the per-instance iteration
                            kernels (tile height 256 or 512 rows): 1 or 2, or
                            0 = tuned on the first solve of each
@@ -193,11 +194,12 @@ typedef struct {
                            as 1 when every shared reference mode passes the
                            test, else 0.  0: W stored and read whole      */
   int32_t graph;        /* 1 (default): each chunk of check_every iterations
-                           that runs as a kernel per step is captured once into a HIP graph (per kernel
-                           arguments) and replayed on a private stream of the
-                           context, ordered against its stream by events;
-                           0: kernels launched one by one.  profile = 1
-                           launches one by one                             */
+                           that runs as a kernel per step is captured once
+                           into a HIP graph (per kernel arguments) and
+                           replayed on a private stream of the context,
+                           ordered against its stream by events; 0: kernels
+                           launched one by one.  profile = 1 launches one by
+                           one                                             */
   int32_t ritz_keep;    /* Rayleigh-Ritz reselection (Sec. "Ritz
                            re-selection"): 0 (default) off; 0 < r: after
                            restriction and orthonormalisation the kept

@@ -1667,8 +1667,9 @@ int reset_solve_state(adef2_ctx* c) {
   return ADEF2_OK;
 }
 
-// Variant of the iteration kernels: rows per thread (tile height) and
-// whether W is read each iteration.  Fixed by the options, or tuned once per
+// Variant of the iteration kernels (a kernel per step): rows per thread (tile
+// height) and whether W is read each iteration.  It only stands by, untuned, where
+// a solve starts with chunk launches.  Fixed by the options, or tuned once per
 // (batch size, precision, basis width, operator form, N) on the first solve:
 // every candidate runs the solve's first two chunks of iterations from the
 // same start and the fastest is kept for this context, so repeated solves of

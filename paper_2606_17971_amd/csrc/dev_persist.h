@@ -18,8 +18,8 @@
 //     arithmetic produces, until its value arrives.  The slots rotate by three:
 //     a block reaches iteration i only after every block of its team has read
 //     the sums of iteration i - 2, so it may clear those then.
-// What bounds it: the four waits (1.2 us each for 16 tiles, 3 us for 128),
-// then the panel products.  Whole solves, one kernel per step against this:
+// What bounds it: the four waits (1 us each with 16 blocks, 1.4-2 us with 64, 3 us
+// with 256), then the panel products.  Whole solves, one kernel per step against this:
 // 63^2, k = 16, FP64 34.6 / 10.1 ms; 255^2, k = 40, FP64 427 / 182 ms;
 // 191^2 x 5, k = 32, mixed 201 / 101 ms; 127^2 x 16 with learned vectors
 // (k = 40 per instance), FP64 108 / 60 ms; 100^2 x 30 active-set loop, k = 40,
@@ -422,7 +422,13 @@ k_persist(IterArgs<V, M> a, PersistArgs pa) {
     double* p = v < NV ? pa.dots + (sl * all + team + tile) * NV + v : pa.pw + sl * all + team + tile;
     st_agent((unsigned long long*)p, PS_EMPTY);
   }
-  if (!ps_handshake(pa) || idle) return;
+  // (S->off: for a reader of the states; the host goes by the words.  Without the
+  // two marks the compiler spills other registers: 100^2 x 30, k = 40 111 -> 113 ms)
+  if (!ps_handshake(pa)) {
+    if (tile == 0 && t0_ == 0) S->off = 1;
+    return;
+  }
+  if (idle) return;
   ps_stall(pa, tile);
 
   const int64_t N = a.op.N;
@@ -770,6 +776,7 @@ k_persist(IterArgs<V, M> a, PersistArgs pa) {
       S->status = status;
       if (done) S->done = 1;
       if (outer_done) S->outer_done = 1;
+      if (!ok) S->off = 2;
     }
   }
 }
