@@ -265,6 +265,13 @@ def test_called_off_launches_step_back(lib, prec, n, k, B):
             tries.append(s.chunk_variant()["called_off"])
         if from_launch == 0:
             assert tries == [1, 1, 2, 2, 2, 2, 2], tries
+            # half-way, with the tuned variant standing by
+            s.fault(1, 2)
+            tuned = s.variant()[:2]
+            out = s.solve_batched(masks, bs, tol)
+            assert s.chunk_variant()["launches"] > 0 and s.chunk_variant()["called_off"] == 3
+            assert s.variant()[:2] == tuned
+            _check(lib, w, S, out, prec, (0, B - 1), tol)
         s.fault(0)
         out = s.solve_batched(masks, bs, tol)
         assert s.chunk_variant()["form"] > 0
